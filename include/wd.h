@@ -59,10 +59,11 @@
  *                         line per key)
  *   WD_TUNE_VERBOSE=1     print every timed candidate to stderr
  *   WD_DSLASH_SHAPE=...   force one shape:
- *                         "nr,gslow,nsub[,link_nt[,out_nt[,wgs[,lds[,rloop[,block]]]]]]"
+ *                         "nr,gslow,nsub[,link_nt[,out_nt[,wgs[,lds[,rloop[,block[,split]]]]]]]"
  *                         (RHS slots per thread, RHS-group order, y-sub-slabs,
  *                         cache hints, workgroups per CU cap, LDS staging,
- *                         binary16 RHS loop, workgroup size)
+ *                         binary16 RHS loop, workgroup size, one wavefront per
+ *                         hop: small launches, the other fields do not apply)
  */
 #ifndef WD_H
 #define WD_H

@@ -329,14 +329,15 @@ struct FinArgs {
   int restart;   // 1: defect correction (Algorithm 1), 0: reliable updates (Algorithm 2)
 };
 
-__global__ void __launch_bounds__(kBlock) k_finalize(int stage, int nb, const double* __restrict__ partials,
+__global__ void __launch_bounds__(kBlock) k_finalize(int stage, int nb, int waves,
+                                                     const double* __restrict__ partials,
                                                      double* __restrict__ sc, int* __restrict__ fl,
                                                      int* __restrict__ active, int* __restrict__ rumask,
                                                      const int* __restrict__ mask, FinArgs fa) {
   const int rhs = blockIdx.x;
   if (mask && !mask[rhs]) return;
   double v[4];  // component 3: FIN_TRUE_RHO only (other stages leave it unset)
-  sum_partials<4>(partials + (int64_t)rhs * nb * kMaxDot, nb, v);
+  sum_partials<4>(partials + (int64_t)rhs * nb * (waves ? 4 : 1) * kMaxDot, nb, waves != 0, v);
   if (threadIdx.x != 0) return;
   double* s = sc + rhs * SC_COUNT;
   int* f = fl + rhs * FL_COUNT;
@@ -619,10 +620,10 @@ hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r6
   });
 }
 
-hipError_t solver_finalize(int stage, int nrhs, int nb, const double* partials, double* sc, int* fl,
+hipError_t solver_finalize(int stage, int nrhs, int nb, int waves, const double* partials, double* sc, int* fl,
                            int* active, int* rumask, const int* mask, double delta, double tol,
                            int restart, hipStream_t s) {
-  k_finalize<<<nrhs, kBlock, 0, s>>>(stage, nb, partials, sc, fl, active, rumask, mask,
+  k_finalize<<<nrhs, kBlock, 0, s>>>(stage, nb, waves, partials, sc, fl, active, rumask, mask,
                                      FinArgs{delta, tol, restart});
   return hipGetLastError();
 }

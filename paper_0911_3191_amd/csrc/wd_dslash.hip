@@ -38,11 +38,20 @@ hipError_t launch_dslash_ex(const wd_gauge* g, wd_prec prec, const DslashArgs& d
                            !d.enc_xh || d.enc_prec < WD_FP32 || d.enc_prec > WD_HALF_F16))
     return hipErrorInvalidValue;
   LaunchCfg c = tuned_dslash_config(g, prec, d, s);
+  const int dot = d.xpay ? d.dot : DOT_NONE;
+  if (c.split) {
+    // built for the forms that the operators and solvers launch; a fused dot
+    // needs room for its wave records
+    const bool form = dot == DOT_NONE || (d.wave_partials && d.waves && (d.dagger ? dot == DOT_ENC : dot != DOT_ENC));
+    const int64_t blocks = ((int64_t)g->geom.Vh / 64 + 32) * (d.rhs_map ? d.n_map : d.out.nrhs);
+    if (!form || blocks > (1 << 22)) c.split = 0;
+  }
+  if (d.waves && dot != DOT_NONE) *d.waves = c.split;
   // A fused dot sums each workgroup's sites into one partial record; with one
   // sub-slab and 256-thread workgroups those site sets are fixed whatever the
   // other fields are, so the reduction -- and the solver -- give the same bits
   // for every tuned shape.
-  if (d.xpay && d.dot != DOT_NONE) {
+  if (dot != DOT_NONE) {
     c.nsub = 1;
     c.block = 256;
   }

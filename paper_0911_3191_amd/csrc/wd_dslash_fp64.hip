@@ -1,6 +1,6 @@
 // Dslash kernels of one storage format (SF64) on DeGrand-Rossi-basis fields;
 // see wd_dslash_impl.h.
-#include "wd_dslash_impl.h"
+#include "wd_dslash_split.h"
 
 namespace wd {
 

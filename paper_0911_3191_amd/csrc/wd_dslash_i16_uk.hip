@@ -1,6 +1,6 @@
 // Dslash kernels of one storage format (SI16) on UKQCD-basis fields, the
 // basis the solvers work in; see wd_dslash_impl.h.
-#include "wd_dslash_impl.h"
+#include "wd_dslash_split.h"
 
 namespace wd {
 

@@ -1098,15 +1098,26 @@ __device__ __forceinline__ void acc_norm(T& nn, const cx<R>& u) {
 // Per right-hand side after the hops: xpay, residual, store (or re-encode)
 // and the fused FP64 partial dot products of one workgroup.  Every thread of
 // the block calls it for the same r (the reductions synchronise the block).
-template <class S, bool XPAY, int DOT, class S2>
+// WAVE: one wavefront works alone; its x and y come in xw, yw and it writes
+// wave records (see wave_sum_store).
+template <int N, bool WAVE>
+__device__ __forceinline__ void sum_store(double (&d)[N], double* out) {
+  if constexpr (WAVE) wave_sum_store<N>(d, out);
+  else block_sum_store<N>(d, out);
+}
+
+template <class S, bool XPAY, int DOT, class S2, bool WAVE = false>
 __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename S::real>& acc, int r, int cb,
                                            bool valid, int pid, FieldView out, FieldView xs, FieldView ys,
-                                           typename S::real a, double* __restrict__ partials, const EncView& enc) {
+                                           typename S::real a, double* __restrict__ partials, const EncView& enc,
+                                           const Spinor<typename S::real>* xw = nullptr,
+                                           const Spinor<typename S::real>* yw = nullptr) {
   using R = typename S::real;
   Spinor<R> x;
   if (valid) {
     if constexpr (XPAY) {
-      load_spinor<S>(xs, r, cb, x);
+      if constexpr (WAVE) x = *xw;
+      else load_spinor<S>(xs, r, cb, x);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -1115,7 +1126,8 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
     }
     if constexpr (DOT == DOT_RES || DOT == DOT_RES_ENC) {
       Spinor<R> b;
-      load_spinor<S>(ys, r, cb, b);
+      if constexpr (WAVE) b = *yw;
+      else load_spinor<S>(ys, r, cb, b);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -1149,7 +1161,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
       d[0] = n2;
     }
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
-    block_sum_store<1>(d, partials + ((int64_t)r * nb + pid) * kMaxDot);
+    sum_store<1, WAVE>(d, partials + ((int64_t)r * nb + pid) * kMaxDot);
   }
   if constexpr (DOT == DOT_RES_ENC) {
     using R2 = typename S2::real;
@@ -1185,7 +1197,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
       d[3] = im;
     }
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
-    block_sum_store<4>(d, partials + ((int64_t)r * nb + pid) * kMaxDot);
+    sum_store<4, WAVE>(d, partials + ((int64_t)r * nb + pid) * kMaxDot);
   }
   if constexpr (DOT != DOT_NONE && DOT != DOT_RES_ENC && DOT != DOT_ENC) {
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
@@ -1194,7 +1206,8 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
       double d[2] = {0.0, 0.0};
       if (valid) {
         Spinor<R> y;
-        load_spinor<S>(ys, r, cb, y);
+        if constexpr (WAVE) y = *yw;
+        else load_spinor<S>(ys, r, cb, y);
         R re = 0, im = 0;
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -1203,7 +1216,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         d[0] = re;
         d[1] = im;
       }
-      block_sum_store<2>(d, part);
+      sum_store<2, WAVE>(d, part);
     } else if constexpr (DOT == DOT_OX) {
       double d[3] = {0.0, 0.0, 0.0};
       if (valid) {
@@ -1219,7 +1232,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         d[1] = im;
         d[2] = nn;
       }
-      block_sum_store<3>(d, part);
+      sum_store<3, WAVE>(d, part);
     } else {
       double d[1] = {0.0};
       if (valid) {
@@ -1230,7 +1243,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
           for (int c = 0; c < 3; ++c) acc_norm(nn, acc.v[s][c]);
         d[0] = nn;
       }
-      block_sum_store<1>(d, part);
+      sum_store<1, WAVE>(d, part);
     }
   }
 }
@@ -1788,8 +1801,16 @@ static bool lds_usable(const wd_gauge* gg, wd_prec prec, const LaunchCfg& c) {
   return lds_stage_bytes(g, nr) <= 63488;
 }
 
+// One wavefront per hop (wd_dslash_split.h).
+template <class S, int BASIS>
+static void launch_split(const wd_gauge* gg, const DslashArgs& d, hipStream_t s);
+
 template <class S, int BASIS>
 static void launch_cfg(const wd_gauge* gg, const DslashArgs& d, const LaunchCfg& c, hipStream_t s) {
+  if (c.split) {
+    launch_split<S, BASIS>(gg, d, s);
+    return;
+  }
   if constexpr (S::prec == WD_HALF_F16) {
     if (c.rloop && gg->recon == 12) {
       launch_rloop<BASIS>(gg, d, c, s);

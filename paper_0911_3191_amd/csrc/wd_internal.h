@@ -90,6 +90,11 @@ struct DslashArgs {
   int dot = DOT_NONE;
   const Field* y = nullptr;
   double* partials = nullptr;
+  // With a fused dot: room for four times the partial records (the split
+  // kernel writes one per 64 sites; null: it is not used), and where the
+  // launch says whether it wrote those (1) or `partials` (0).
+  double* wave_partials = nullptr;
+  int* waves = nullptr;
   const int* active = nullptr;  // device mask [nrhs]: RHS with 0 are skipped
   // Device list of n_map RHS indices (distinct, < out.nrhs): only those are
   // processed, packed into as few RHS groups as they fill (replaces `active`).
@@ -122,6 +127,7 @@ struct LaunchCfg {
   int wgs = 0;      // cap on workgroups per CU (0: registers decide)
   int lds = 0;      // 16-bit formats: stage x/y neighbours in LDS
   int rloop = 0;    // binary16, 12-real links: one thread per site loops over every RHS
+  int split = 0;    // one wavefront per hop (small launches); the fields above do not apply
 };
 void launch_dslash_cfg(const wd_gauge* g, wd_prec prec, const DslashArgs& d, const LaunchCfg& c,
                        hipStream_t s);
@@ -223,7 +229,8 @@ hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r6
                          const int* mask, double* partials, hipStream_t s, bool set_rt = false);
 // restart = 1 (defect correction): the update trigger compares |r^| with the
 // residual the inner solve started from, and CG restarts with beta = 0.
-hipError_t solver_finalize(int stage, int nrhs, int nb, const double* partials, double* sc, int* fl,
+// waves: the records are wave records, four to each of the nb (DslashArgs::waves).
+hipError_t solver_finalize(int stage, int nrhs, int nb, int waves, const double* partials, double* sc, int* fl,
                            int* active, int* rumask, const int* mask, double delta, double tol,
                            int restart, hipStream_t s);
 hipError_t solver_cg_tighten(int nrhs, double* sc, const int* fl, const int* mask, double tol,

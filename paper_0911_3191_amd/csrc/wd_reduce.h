@@ -44,16 +44,40 @@ __device__ __forceinline__ void block_sum_store(double (&v)[N], double* out) {
   __syncthreads();
 }
 
+// Sum v[0..N) over one wavefront; lane 0 writes out[0..N).  The four wave
+// records of 256 consecutive sites, added as (r0 + r1) + (r2 + r3), are the
+// bits of block_sum_store's record of those sites.
+template <int N>
+__device__ __forceinline__ void wave_sum_store(double (&v)[N], double* out) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += __shfl_down(v[k], off, 64);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < N; ++k) out[k] = v[k];
+}
+
 // Fixed-order sum of nb partial records (stride kMaxDot) into res[0..N).
 // Called by all threads of one block; the result is valid in thread 0.  Ends
 // with a barrier so that a second call may reuse the LDS slots at once.
+// waves: each record is four wave records (see wave_sum_store).
 template <int N>
-__device__ __forceinline__ void sum_partials(const double* part, int nb, double (&res)[N]) {
+__device__ __forceinline__ void sum_partials(const double* part, int nb, bool waves, double (&res)[N]) {
 #pragma unroll
   for (int k = 0; k < N; ++k) res[k] = 0.0;
-  for (int i = threadIdx.x; i < nb; i += kBlock)
+  if (waves) {
+    for (int i = threadIdx.x; i < nb; i += kBlock) {
+      const double* q = part + (int64_t)i * 4 * kMaxDot;
 #pragma unroll
-    for (int k = 0; k < N; ++k) res[k] += part[(int64_t)i * kMaxDot + k];
+      for (int k = 0; k < N; ++k)
+        res[k] += (q[k] + q[kMaxDot + k]) + (q[2 * kMaxDot + k] + q[3 * kMaxDot + k]);
+    }
+  } else {
+    for (int i = threadIdx.x; i < nb; i += kBlock)
+#pragma unroll
+      for (int k = 0; k < N; ++k) res[k] += part[(int64_t)i * kMaxDot + k];
+  }
   __shared__ double sm[N][kBlock];
 #pragma unroll
   for (int k = 0; k < N; ++k) sm[k][threadIdx.x] = res[k];

@@ -68,6 +68,8 @@ struct wd_solver {
   double* x_out;
   const double* b_in;
   int nrhs, nb, nb_dslash;  // partial records per RHS: BLAS-1 kernels, fused-dot dslash
+  int waves;                // the last fused-dot dslash wrote wave records into wave_records
+  double* wave_records;
   wd::Field bhat, x, r, rn, to64;
   wd::Field rh, rt, p, v, t, xh, to;  // CG uses v as q and t as w; rt unused
   double* partials;
@@ -92,6 +94,17 @@ struct wd_solver {
 
 namespace wd {
 
+// Room for the wave records of a fused dot: whichever odd temporary the launch
+// does not use (the FP64 one is free while the inner solver iterates, the
+// inner one during prepare and the reliable updates).
+static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d) {
+  const bool hi = d.in.ptr == h->to64.ptr || d.out.ptr == h->to64.ptr || (d.xpay && d.xpay->ptr == h->to64.ptr);
+  h->wave_records = reinterpret_cast<double*>(hi ? h->to.ptr : h->to64.ptr);
+  d.wave_partials = h->wave_records;
+  d.waves = &h->waves;
+  return launch_dslash_ex(h->g, prec, d, h->s);
+}
+
 // With n_map > 0 the launch covers only the n_map RHS listed in h->rumap (the
 // same set as mask), packed into as few RHS groups as they fill.
 static hipError_t dslash_into(wd_solver* h, wd_prec prec, const Field& out, const Field& in,
@@ -113,7 +126,7 @@ static hipError_t dslash_into(wd_solver* h, wd_prec prec, const Field& out, cons
     d.rhs_map = h->rumap;
     d.n_map = n_map;
   }
-  return launch_dslash_ex(h->g, prec, d, h->s);
+  return launch_dot(h, prec, d);
 }
 
 // out_e = in_e - kappa^2 D_eo D_oe in_e (dagger: the adjoint), optional fused dot.
@@ -128,8 +141,9 @@ static hipError_t mhat_into(wd_solver* h, wd_prec prec, const Field& out, const 
 // after_dslash: the partial records come from a dslash with a fused dot
 // (its record count per RHS), else from a BLAS-1 kernel.
 static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash) {
-  return solver_finalize(stage, h->nrhs, after_dslash ? h->nb_dslash : h->nb, h->partials, h->sc,
-                         h->fl, h->active, h->rumask, mask, h->prm.delta, h->prm.tol, h->prm.restart,
+  const int waves = after_dslash ? h->waves : 0;
+  return solver_finalize(stage, h->nrhs, after_dslash ? h->nb_dslash : h->nb, waves,
+                         waves ? h->wave_records : h->partials, h->sc, h->fl, h->active, h->rumask, mask, h->prm.delta, h->prm.tol, h->prm.restart,
                          h->s);
 }
 
@@ -240,7 +254,7 @@ static hipError_t true_residual(wd_solver* h, const int* mask, int n_map = 0, bo
   d.enc_xh = &h->xh;
   d.enc_rt = &h->rt;
   d.enc_set_rt = h->prm.restart;
-  WD_TRY(launch_dslash_ex(h->g, WD_FP64, d, h->s));
+  WD_TRY(launch_dot(h, WD_FP64, d));
   WD_TRY(fin(h, !reencode ? FIN_TRUE : (h->prm.restart ? FIN_TRUE_INIT : FIN_TRUE_RHO), mask, true));
   if (reencode && h->prm.restart) {  // p = v = 0 where the restarted solve goes on
     WD_TRY(blas_zero(h->geom, h->prm.inner, h->p, h->rumask, h->s));
@@ -295,7 +309,7 @@ static hipError_t reseed(wd_solver* h, bool first, const Field& r64, int n_map =
         d.rhs_map = h->rumap;
         d.n_map = n_map;
       }
-      WD_TRY(launch_dslash_ex(h->g, WD_FP64, d, h->s));
+      WD_TRY(launch_dot(h, WD_FP64, d));
     }
     WD_TRY(fin(h, first ? FIN_CG_INIT : FIN_CG_RHO, h->rumask, fused));
     if (first) WD_TRY(blas_convert(g, P, h->p, P, h->rh, h->rumask, h->s));  // p = r^

@@ -86,7 +86,8 @@ bool valid_cfg(const LaunchCfg& c) {
   const bool block_ok = c.block == 128 || c.block == 256 || (c.rloop && c.block == 512);
   return block_ok && c.nr >= 1 && c.nr <= 4 && !(c.rloop && c.nr != 1) && (c.gslow == 0 || c.gslow == 1) &&
          c.nsub >= 1 && c.nsub <= 8 && (c.link_nt == 0 || c.link_nt == 1) && (c.out_nt == 0 || c.out_nt == 1) &&
-         (c.wgs == 0 || (c.wgs >= 2 && c.wgs <= 8)) && (c.lds == 0 || c.lds == 1) && (c.rloop == 0 || c.rloop == 1);
+         (c.wgs == 0 || (c.wgs >= 2 && c.wgs <= 8)) && (c.lds == 0 || c.lds == 1) && (c.rloop == 0 || c.rloop == 1) &&
+         (c.split == 0 || c.split == 1);
 }
 
 const char* cache_path() {
@@ -288,16 +289,45 @@ LaunchCfg run_tuner(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStr
 
 }  // namespace
 
+// Where one wavefront per hop (wd_dslash_split.h) replaces the searched
+// shapes: by the bytes of the launch (links once, every right-hand side's
+// input and output), so that the choice needs no timing.  It wins while the
+// launch stays in the 256 MB last-level cache, where the one-thread kernels
+// wait on latency with the bandwidth unused, and loses once HBM sets the
+// pace.  Measured, best one-thread shape against it in microseconds: FP64
+// 24^3x32 (255 MB) 61 / 45, 24^3x48 (382 MB) 84 / 88, 16^3x32 with 12
+// right-hand sides (352 MB) 121 / 157; FP32 32^3x32 (302 MB) 60 / 55, 32^3x64
+// (604 MB) 120 / 129; one 16-bit right-hand side 32^3x32 (155 MB) 36 / 29,
+// 32^3x64 (310 MB) 64 / 71.  Several 16-bit right-hand sides share their links
+// in the one-thread kernels, and the rebuilt third row is a large part of
+// their work: level from about 131,072 site right-hand sides (16^3x32 with 2:
+// 10.4 / 10.3, 20x14x10x18 with 5: 10.2 / 10.6, with 12: 17.0 / 18.5).
+static bool split_pays(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
+  const int64_t Vh = g->geom.Vh, n = launch_rhs(d);
+  const int64_t site = is_half(prec) ? 52 : (prec == WD_FP64 ? 192 : 96);
+  const int64_t bytes = Vh * (8 * link_bytes(prec, g->recon) + 2 * n * site);
+  if (is_half(prec)) return n == 1 ? bytes <= (200 << 20) : Vh * n <= (1 << 17);
+  return bytes <= (prec == WD_FP64 ? (256 << 20) : (300 << 20));
+}
+
+static LaunchCfg searched_config(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStream_t s);
+
 LaunchCfg tuned_dslash_config(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStream_t s) {
-  const int nrhs = launch_rhs(d);
   // WD_DSLASH_SHAPE forces one shape (tests sweep them with it)
   if (const char* f = std::getenv("WD_DSLASH_SHAPE")) {
-    int nr = 1, gslow = 0, nsub = 1, nt = 0, ont = 0, wgs = 0, lds = 0, rloop = 0, block = 256;
-    const int n = std::sscanf(f, "%d,%d,%d,%d,%d,%d,%d,%d,%d", &nr, &gslow, &nsub, &nt, &ont, &wgs, &lds, &rloop,
-                              &block);
-    const LaunchCfg c{nr, block, gslow, nsub, nt, ont, wgs, lds, rloop};
+    int nr = 1, gslow = 0, nsub = 1, nt = 0, ont = 0, wgs = 0, lds = 0, rloop = 0, block = 256, split = 0;
+    const int n = std::sscanf(f, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &nr, &gslow, &nsub, &nt, &ont, &wgs, &lds,
+                              &rloop, &block, &split);
+    const LaunchCfg c{nr, block, gslow, nsub, nt, ont, wgs, lds, rloop, split};
     if (n >= 3 && valid_cfg(c)) return c;
   }
+  LaunchCfg c = searched_config(g, prec, d, s);
+  c.split = split_pays(g, prec, d);
+  return c;
+}
+
+static LaunchCfg searched_config(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStream_t s) {
+  const int nrhs = launch_rhs(d);
   const Key k = key_of(g, prec, d);
   {
     std::lock_guard<std::mutex> lock(g_mu);
