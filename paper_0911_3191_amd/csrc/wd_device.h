@@ -244,4 +244,31 @@ __device__ __forceinline__ const char* link_chunk(const char* base, int64_t stri
   return base + ((int64_t)((par * 4 + mu) * LinkChunks<S>::N + k) * stride) * LinkChunks<S>::BYTES;
 }
 
+// ---- canonical link records through LDS ------------------------------------------
+// A workgroup of 256 threads owns the links of 64 consecutive lexicographic
+// sites, one contiguous block of the canonical array [V][4][3][3] (144 bytes
+// a link).  It is moved 16 bytes a lane in address order; thread (mu, site) =
+// (threadIdx.x / 64, threadIdx.x % 64) then works on link mu of its site.  A
+// site takes 37 slots of 16 bytes (36 and one of padding), which spreads the
+// lanes of a wavefront over all banks.  One thread per record straight from
+// memory touches 64 lines with each instruction instead.
+constexpr int kLinkSites = 64, kLinkThreads = 256, kLinkRow = 37;
+using LinkTile = double2[kLinkSites * kLinkRow];
+
+// Links of the n sites from L0 on into the tile (the caller synchronises).
+__device__ __forceinline__ void load_links(const double* __restrict__ U, int64_t L0, int n, double2* tile) {
+  const double2* src = reinterpret_cast<const double2*>(U) + L0 * 36;
+  double2 v[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) v[k] = src[min(k * kLinkThreads + (int)threadIdx.x, 36 * n - 1)];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int idx = k * kLinkThreads + threadIdx.x;
+    tile[(idx / 36) * kLinkRow + idx % 36] = v[k];
+  }
+}
+__device__ __forceinline__ const double2* link_record(const double2* tile, int mu, int site) {
+  return tile + site * kLinkRow + 9 * mu;
+}
+
 }  // namespace wd

@@ -24,6 +24,17 @@ __device__ __forceinline__ int64_t lex_of(const SiteMap& m, int cb, int p) {
   return x + (int64_t)m.L[0] * (y + (int64_t)m.L[1] * (z + (int64_t)m.L[2] * t));
 }
 
+// Parity of lexicographic site L; its checkerboard index is L / 2 (Lx is even).
+__device__ __forceinline__ int parity_of(const SiteMap& m, int L) {
+  const int row = L / m.L[0];
+  const int x = L - row * m.L[0];
+  const int y = row % m.L[1];
+  const int zt = row / m.L[1];
+  const int z = zt % m.L[2];
+  const int t = zt / m.L[2];
+  return (x + y + z + t) & 1;
+}
+
 static SiteMap site_map(const Geom& g) {
   SiteMap m;
   for (int k = 0; k < 4; ++k) m.L[k] = g.L[k];
@@ -33,18 +44,26 @@ static SiteMap site_map(const Geom& g) {
 }
 
 // ---- gauge ------------------------------------------------------------------------
-// One thread per (site cb, parity, mu): rows a, b of U[lex][mu] into every
-// precision of the mask.  16-bit: int16 q = rint(u * 32767) or binary16 u.
-__global__ void gauge_encode_kernel(SiteMap m, const double* __restrict__ U, int64_t stride,
-                                    char* f64, char* f32, char* i16, char* h16) {
-  const int cb = blockIdx.x * blockDim.x + threadIdx.x;
-  const int par = blockIdx.y >> 2, mu = blockIdx.y & 3;
-  if (cb >= m.Vh) return;
-  const int64_t lex = lex_of(m, cb, par);
-  const double* u = U + (lex * 4 + mu) * 18;  // rows a, b are the first 12 reals
+// One thread per (site, mu): rows a, b of U[lex][mu] into every precision of
+// the mask.  16-bit: int16 q = rint(u * 32767) or binary16 u.
+__global__ void __launch_bounds__(kLinkThreads) gauge_encode_kernel(SiteMap m, const double* __restrict__ U,
+                                                                    int64_t stride, char* f64, char* f32, char* i16,
+                                                                    char* h16) {
+  __shared__ LinkTile tile;
+  const int L0 = blockIdx.x * kLinkSites;
+  const int n = min(kLinkSites, 2 * m.Vh - L0);
+  load_links(U, L0, n, tile);
+  __syncthreads();
+  const int site = threadIdx.x & 63, mu = threadIdx.x >> 6;
+  if (site >= n) return;
+  const int par = parity_of(m, L0 + site), cb = (L0 + site) >> 1;
+  const double2* rec = link_record(tile, mu, site);  // rows a, b are the first 12 reals
   double v[12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) v[k] = u[k];
+  for (int k = 0; k < 6; ++k) {
+    v[2 * k] = rec[k].x;
+    v[2 * k + 1] = rec[k].y;
+  }
   if (f64) {
 #pragma unroll
     for (int k = 0; k < 6; ++k)
@@ -87,9 +106,7 @@ __global__ void gauge_encode_kernel(SiteMap m, const double* __restrict__ U, int
 
 hipError_t launch_gauge_encode(const wd_gauge* g, const double* U, hipStream_t s) {
   SiteMap m = site_map(g->geom);
-  const int block = 256;
-  dim3 grid((m.Vh + block - 1) / block, 8);
-  gauge_encode_kernel<<<grid, block, 0, s>>>(
+  gauge_encode_kernel<<<(2 * m.Vh + kLinkSites - 1) / kLinkSites, kLinkThreads, 0, s>>>(
       m, U, g->geom.stride, static_cast<char*>(g->link[WD_FP64]), static_cast<char*>(g->link[WD_FP32]),
       static_cast<char*>(g->link[WD_HALF_I16]), static_cast<char*>(g->link[WD_HALF_F16]));
   return hipGetLastError();
@@ -249,17 +266,6 @@ __global__ void __launch_bounds__(kTileSites) spinor_decode_kernel(SiteMap m, Fi
   double* dst = canon + (int64_t)r * (FULL ? 2 : 1) * m.Vh * 24;
   const int rec = FULL ? (int)lex_of(m, min(cb, m.Vh - 1), parity) : cb;
   move_records<!FULL, true>(reinterpret_cast<double2*>(dst), tile, rec, n);
-}
-
-// Parity of lexicographic site L; its checkerboard index is L / 2 (Lx is even).
-__device__ __forceinline__ int parity_of(const SiteMap& m, int L) {
-  const int row = L / m.L[0];
-  const int x = L - row * m.L[0];
-  const int y = row % m.L[1];
-  const int zt = row / m.L[1];
-  const int z = zt % m.L[2];
-  const int t = zt / m.L[2];
-  return (x + y + z + t) & 1;
 }
 
 // Both parities of a canonical full lattice [nrhs][V][24] (FP64 fields) in one
