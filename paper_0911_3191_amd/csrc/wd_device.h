@@ -168,16 +168,20 @@ __device__ __forceinline__ void st16(V* p, V v) {
   else *p = v;
 }
 
-// Encode 24 reals of the arithmetic type into one site of the field.
+// Encode 24 reals of the arithmetic type into one site of the field.  With
+// `back`, also the values that load_spinor would read back (16-bit formats:
+// rounded), without the round trip through memory.
 template <class S, bool NT = false>
 __device__ __forceinline__ void store_spinor(const FieldView& f, int r, int64_t i,
-                                             const Spinor<typename S::real>& s) {
+                                             const Spinor<typename S::real>& s,
+                                             Spinor<typename S::real>* back = nullptr) {
   if constexpr (S::prec == WD_FP64) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
       cx<double> z = s.v[k / 3][k % 3];
       st16<NT>(reinterpret_cast<dvec2*>(const_cast<char*>(chunk_base<S>(f, r, k))) + i, dvec2{z.re, z.im});
     }
+    if (back) *back = s;
   } else if constexpr (S::prec == WD_FP32) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -185,6 +189,7 @@ __device__ __forceinline__ void store_spinor(const FieldView& f, int r, int64_t 
       st16<NT>(reinterpret_cast<fvec4*>(const_cast<char*>(chunk_base<S>(f, r, k))) + i,
                fvec4{a.re, a.im, b.re, b.im});
     }
+    if (back) *back = s;
   } else {
     float nm = 0.0f;
 #pragma unroll
@@ -199,6 +204,7 @@ __device__ __forceinline__ void store_spinor(const FieldView& f, int r, int64_t 
     float sc;
     if constexpr (S::prec == WD_HALF_I16) sc = (nm > 0.0f) ? 32767.0f / nm : 0.0f;
     else sc = (nm > 0.0f) ? 1.0f / nm : 0.0f;
+    const float bs = (S::prec == WD_HALF_I16) ? nm / 32767.0f : nm;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       uint32_t w[4];
@@ -217,6 +223,10 @@ __device__ __forceinline__ void store_spinor(const FieldView& f, int r, int64_t 
           hi = f_to_h16(pin_f32(z.im * sc));
         }
         w[j] = (uint32_t)lo | ((uint32_t)hi << 16);
+        if (back) {
+          if constexpr (S::prec == WD_HALF_I16) back->v[n / 3][n % 3] = {(float)(int16_t)lo * bs, (float)(int16_t)hi * bs};
+          else back->v[n / 3][n % 3] = {h16_to_f(lo) * bs, h16_to_f(hi) * bs};
+        }
       }
       st16<NT>(reinterpret_cast<uvec4*>(const_cast<char*>(chunk_base<S>(f, r, k))) + i,
                uvec4{w[0], w[1], w[2], w[3]});

@@ -1150,14 +1150,14 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
           e.v[s][c] = {static_cast<R2>(acc.v[s][c].re), static_cast<R2>(acc.v[s][c].im)};
           z.v[s][c] = {R2(0), R2(0)};
         }
-      store_spinor<S2>(enc.rh, r, cb, e);
+      Spinor<R2> back;  // the norm of the stored (re-encoded) value
+      store_spinor<S2>(enc.rh, r, cb, e, &back);
       store_spinor<S2>(enc.xh, r, cb, z);
-      load_spinor<S2>(enc.rh, r, cb, e);  // the norm of the stored (re-encoded) value
       R2 n2 = 0;
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) acc_norm(n2, e.v[s][c]);
+        for (int c = 0; c < 3; ++c) acc_norm(n2, back.v[s][c]);
       d[0] = n2;
     }
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
@@ -1177,19 +1177,22 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
           e.v[s][c] = {static_cast<R2>(acc.v[s][c].re), static_cast<R2>(acc.v[s][c].im)};
           z.v[s][c] = {R2(0), R2(0)};
         }
-      store_spinor<S2>(enc.rh, r, cb, e);
-      store_spinor<S2>(enc.xh, r, cb, z);
-      if (enc.set_rt) store_spinor<S2>(enc.rt, r, cb, e);
       // the dots see the stored (re-encoded) residual
-      load_spinor<S2>(enc.rh, r, cb, e);
-      load_spinor<S2>(enc.rt, r, cb, t);
+      Spinor<R2> back;
+      if (!enc.set_rt) load_spinor<S2>(enc.rt, r, cb, t);
+      store_spinor<S2>(enc.rh, r, cb, e, &back);
+      store_spinor<S2>(enc.xh, r, cb, z);
+      if (enc.set_rt) {
+        store_spinor<S2>(enc.rt, r, cb, e);
+        t = back;
+      }
       R2 n2 = 0, re = 0, im = 0;
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          acc_norm(n2, e.v[s][c]);
-          acc_cdotc(re, im, t.v[s][c], e.v[s][c]);
+          acc_norm(n2, back.v[s][c]);
+          acc_cdotc(re, im, t.v[s][c], back.v[s][c]);
         }
       d[0] = nn;
       d[1] = n2;

@@ -190,8 +190,9 @@ enum ScalarSlot {
   SC_MMAX = 10,    // max |r^| since the last reliable update (Algorithm 2's M)
   SC_B2 = 11,      // |b|^2 of the full-lattice source
   SC_TOLN = 12,    // CG: target on the normal-equation residual
-  SC_BETA = 13,    // CG: beta
+  SC_BETA = 13,    // beta (BiCGstab, complex: the imaginary part in SC_BETA_IM)
   SC_BNORM = 14,   // |b| of the caller's source (the solve runs on b / |b|)
+  SC_BETA_IM = 15,
   SC_COUNT = 16
 };
 // FL_ITERS counts the inner iterations an RHS has started, on the device, so
@@ -208,6 +209,9 @@ hipError_t blas_bicg_p(const Geom& g, wd_prec pr, Field p, Field r, Field v, con
                        const int* mask, hipStream_t s);
 hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double* sc,
                        const int* mask, hipStream_t s);
+// Partial records per RHS that blas_bicg_xr and blas_cg_xr write (up to four
+// times those of the other kernels).
+int blas_dot_records(const Geom& g, wd_prec p);
 hipError_t blas_bicg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field rt,
                         const double* sc, const int* mask, double* partials, hipStream_t s);
 hipError_t blas_cg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field q,

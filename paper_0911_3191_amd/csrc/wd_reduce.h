@@ -58,39 +58,55 @@ __device__ __forceinline__ void wave_sum_store(double (&v)[N], double* out) {
     for (int k = 0; k < N; ++k) out[k] = v[k];
 }
 
-// Fixed-order sum of nb partial records (stride kMaxDot) into res[0..N).
-// Called by all threads of one block; the result is valid in thread 0.  Ends
-// with a barrier so that a second call may reuse the LDS slots at once.
-// waves: each record is four wave records (see wave_sum_store).
-template <int N>
-__device__ __forceinline__ void sum_partials(const double* part, int nb, bool waves, double (&res)[N]) {
-#pragma unroll
-  for (int k = 0; k < N; ++k) res[k] = 0.0;
+// Fixed-order sum of nb partial records (stride kMaxDot) into res[0..4).
+// Called by all kFinBlock threads of one block; the result is valid in thread
+// 0.  waves: each record is four wave records (see wave_sum_store).  `before`
+// runs before the barrier.
+constexpr int kFinBlock = 512;
+template <class F>
+__device__ __forceinline__ void sum_partials(const double* part, int nb, bool waves, double (&res)[4], F&& before) {
+  struct Rec {
+    double2 a, b;
+  };
+  const Rec* rec = reinterpret_cast<const Rec*>(part);
+  double2 sa = {0.0, 0.0}, sb = {0.0, 0.0};
   if (waves) {
-    for (int i = threadIdx.x; i < nb; i += kBlock) {
-      const double* q = part + (int64_t)i * 4 * kMaxDot;
-#pragma unroll
-      for (int k = 0; k < N; ++k)
-        res[k] += (q[k] + q[kMaxDot + k]) + (q[2 * kMaxDot + k] + q[3 * kMaxDot + k]);
+#pragma unroll 2
+    for (int i = threadIdx.x; i < nb; i += kFinBlock) {
+      const Rec r0 = rec[4 * i], r1 = rec[4 * i + 1], r2 = rec[4 * i + 2], r3 = rec[4 * i + 3];
+      sa.x += (r0.a.x + r1.a.x) + (r2.a.x + r3.a.x);
+      sa.y += (r0.a.y + r1.a.y) + (r2.a.y + r3.a.y);
+      sb.x += (r0.b.x + r1.b.x) + (r2.b.x + r3.b.x);
+      sb.y += (r0.b.y + r1.b.y) + (r2.b.y + r3.b.y);
     }
   } else {
-    for (int i = threadIdx.x; i < nb; i += kBlock)
-#pragma unroll
-      for (int k = 0; k < N; ++k) res[k] += part[(int64_t)i * kMaxDot + k];
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nb; i += kFinBlock) {
+      const Rec r = rec[i];
+      sa.x += r.a.x;
+      sa.y += r.a.y;
+      sb.x += r.b.x;
+      sb.y += r.b.y;
+    }
   }
-  __shared__ double sm[N][kBlock];
+  double v[4] = {sa.x, sa.y, sb.x, sb.y};
 #pragma unroll
-  for (int k = 0; k < N; ++k) sm[k][threadIdx.x] = res[k];
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] += __shfl_down(v[k], off, 64);
+  __shared__ double sm[kFinBlock / 64][4];
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sm[threadIdx.x >> 6][k] = v[k];
+  before();
   __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
 #pragma unroll
-      for (int k = 0; k < N; ++k) sm[k][threadIdx.x] += sm[k][threadIdx.x + w];
-    __syncthreads();
+  for (int k = 0; k < 4; ++k) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFinBlock / 64; ++w) t += sm[w][k];
+    res[k] = t;
   }
-#pragma unroll
-  for (int k = 0; k < N; ++k) res[k] = sm[k][0];
-  __syncthreads();
 }
 
 }  // namespace wd

@@ -138,10 +138,19 @@ static hipError_t mhat_into(wd_solver* h, wd_prec prec, const Field& out, const 
   return dslash_into(h, prec, out, tmp_odd, 0, dagger, &in, -h->kappa * h->kappa, dot, y, mask, n_map);
 }
 
+// Records of the iteration's x/r update: more than h->partials has room for
+// where it splits sites over threads; the FP64 odd temporary is free then.
+static double* xr_records(wd_solver* h) {
+  return blas_dot_records(h->geom, h->prm.inner) <= h->nb ? h->partials : reinterpret_cast<double*>(h->to64.ptr);
+}
+
 // after_dslash: the partial records come from a dslash with a fused dot
 // (its record count per RHS), else from a BLAS-1 kernel.
 static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash) {
   const int waves = after_dslash ? h->waves : 0;
+  if (stage == FIN_BICG_ITER || stage == FIN_CG_ITER)  // after the x/r update
+    return solver_finalize(stage, h->nrhs, blas_dot_records(h->geom, h->prm.inner), 0, xr_records(h), h->sc, h->fl,
+                           h->active, h->rumask, mask, h->prm.delta, h->prm.tol, h->prm.restart, h->s);
   return solver_finalize(stage, h->nrhs, after_dslash ? h->nb_dslash : h->nb, waves,
                          waves ? h->wave_records : h->partials, h->sc, h->fl, h->active, h->rumask, mask, h->prm.delta, h->prm.tol, h->prm.restart,
                          h->s);
@@ -203,14 +212,14 @@ static hipError_t iteration_body(wd_solver* h) {
     WD_TRY(blas_bicg_s(g, P, h->rh, h->v, h->sc, act, h->s));           // s = r - alpha v
     WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, nullptr, act));  // t = M s, <t,s>, |t|^2
     WD_TRY(fin(h, FIN_BICG_OMEGA, act, true));
-    WD_TRY(blas_bicg_xr(g, P, h->xh, h->rh, h->p, h->t, h->rt, h->sc, act, h->partials, h->s));
+    WD_TRY(blas_bicg_xr(g, P, h->xh, h->rh, h->p, h->t, h->rt, h->sc, act, xr_records(h), h->s));
     WD_TRY(fin(h, FIN_BICG_ITER, act, false));
   } else {
     // w = M p (|w|^2), q = M^dag w, x^ += alpha p, r^ -= alpha q
     WD_TRY(mhat_into(h, P, h->t, h->p, h->to, 0, DOT_OO, nullptr, act));
     WD_TRY(fin(h, FIN_CG_ALPHA, act, true));
     WD_TRY(mhat_into(h, P, h->v, h->t, h->to, 1, DOT_NONE, nullptr, act));
-    WD_TRY(blas_cg_xr(g, P, h->xh, h->rh, h->p, h->v, h->sc, act, h->partials, h->s));
+    WD_TRY(blas_cg_xr(g, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), h->s));
     WD_TRY(fin(h, FIN_CG_ITER, act, false));
     // p = r^ + beta p where iteration goes on; an RHS that triggered a
     // reliable update is paused and takes this step after the update
