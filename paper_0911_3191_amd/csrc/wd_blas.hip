@@ -9,7 +9,7 @@
 #include <type_traits>
 
 #include "wd_device.h"
-#include "wd_reduce.h"
+#include "wd_finalize.h"
 
 static_assert(wd::kMaxDot == wd::kMaxDotHost, "partial record size");
 
@@ -18,11 +18,6 @@ namespace wd {
 template <typename R>
 __device__ __forceinline__ cx<R> cload(const double* sc, int k) {
   return {static_cast<R>(sc[k]), static_cast<R>(sc[k + 1])};
-}
-
-__device__ __forceinline__ cx<double> cdiv(cx<double> a, cx<double> b) {
-  const double d = b.re * b.re + b.im * b.im;
-  return {(a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d};
 }
 
 // What a thread of the iteration's updates holds of a site: the whole of it,
@@ -83,16 +78,6 @@ __device__ __forceinline__ void store_part(const FieldView& f, int r, int64_t i,
 }
 
 // ---- BiCGstab ---------------------------------------------------------------------
-// beta = (rho / rho_prev) (alpha / omega) of the next p-update; every finalize
-// stage that changes one of its factors stores it, which keeps four FP64
-// divisions out of every thread of the update.
-__device__ __forceinline__ void store_beta(double* s, cx<double> rho, cx<double> rhop, cx<double> alpha,
-                                           cx<double> omega) {
-  const cx<double> b = cdiv(rho, rhop) * cdiv(alpha, omega);
-  s[SC_BETA] = b.re;
-  s[SC_BETA_IM] = b.im;
-}
-
 // p <- r + beta (p - omega v)
 template <class S, bool SPLIT>
 __global__ void __launch_bounds__(kBlock) k_bicg_p(int Vh, FieldView p, FieldView r, FieldView v,
@@ -141,7 +126,7 @@ __global__ void __launch_bounds__(kBlock) k_bicg_xr(int Vh, FieldView x, FieldVi
                                                     FieldView t, FieldView rt,
                                                     const double* __restrict__ sc,
                                                     const int* __restrict__ mask,
-                                                    double* __restrict__ partials) {
+                                                    double* __restrict__ partials, FinArgs fa) {
   using R = typename S::real;
   const int rhs = blockIdx.y;
   if (mask && !mask[rhs]) return;
@@ -173,7 +158,9 @@ __global__ void __launch_bounds__(kBlock) k_bicg_xr(int Vh, FieldView x, FieldVi
     d[1] = re;
     d[2] = im;
   }
-  block_sum_store<3>(d, partials + ((int64_t)rhs * gridDim.x + blockIdx.x) * kMaxDot);
+  double* rec = partials + (int64_t)rhs * gridDim.x * kMaxDot;
+  if (fa.stage < 0) block_sum_store<3>(d, rec + blockIdx.x * kMaxDot);
+  else block_sum_finalize<3>(d, rec, blockIdx.x, gridDim.x, rhs, fa);
 }
 
 // ---- CG on the normal equations ---------------------------------------------------
@@ -182,7 +169,7 @@ template <class S, bool SPLIT>
 __global__ void __launch_bounds__(kBlock) k_cg_xr(int Vh, FieldView x, FieldView r, FieldView p,
                                                   FieldView q, const double* __restrict__ sc,
                                                   const int* __restrict__ mask,
-                                                  double* __restrict__ partials) {
+                                                  double* __restrict__ partials, FinArgs fa) {
   using R = typename S::real;
   const int rhs = blockIdx.y;
   if (mask && !mask[rhs]) return;
@@ -206,7 +193,9 @@ __global__ void __launch_bounds__(kBlock) k_cg_xr(int Vh, FieldView x, FieldView
     store_part<S, SPLIT>(r, rhs, i, Rr);
     d[0] = nn;
   }
-  block_sum_store<1>(d, partials + ((int64_t)rhs * gridDim.x + blockIdx.x) * kMaxDot);
+  double* rec = partials + (int64_t)rhs * gridDim.x * kMaxDot;
+  if (fa.stage < 0) block_sum_store<1>(d, rec + blockIdx.x * kMaxDot);
+  else block_sum_finalize<1>(d, rec, blockIdx.x, gridDim.x, rhs, fa);
 }
 
 // p <- r + beta p
@@ -380,192 +369,21 @@ __global__ void __launch_bounds__(kBlock) k_reencode(int Vh, FieldView rh, Field
 }
 
 // ---- finalize: partials -> scalars (one block per RHS) ---------------------------------
-struct FinArgs {
-  double delta;  // reliable-update trigger (defect correction: inner tolerance)
-  double tol;    // target relative residual
-  int restart;   // 1: defect correction (Algorithm 1), 0: reliable updates (Algorithm 2)
-};
-
 // What bounds it is latency: the records of one right-hand side are summed by
 // one workgroup, with its scalars in flight meanwhile.  512 threads, wavefront
-// shuffles and one barrier: 8^4 3.0 -> 2.7 us, 24^3x32 with
-// wave records 5.3 -> 5.2 us on average (it waits for other XCDs' records).
-__global__ void __launch_bounds__(kFinBlock) k_finalize(int stage, int nb, int waves,
-                                                     const double* __restrict__ partials,
-                                                     double* __restrict__ sc, int* __restrict__ fl,
-                                                     int* __restrict__ active, int* __restrict__ rumask,
-                                                     const int* __restrict__ mask, FinArgs fa) {
+// shuffles and one barrier: 8^4 3.0 -> 2.7 us, 24^3x32 with wave records
+// 5.3 -> 5.2 us on average (it waits for other XCDs' records).
+__global__ void __launch_bounds__(kFinBlock) k_finalize(int nb, int waves, const double* __restrict__ partials,
+                                                        const int* __restrict__ mask, FinArgs fa) {
   const int rhs = blockIdx.x;
   if (mask && !mask[rhs]) return;
-  double* s = sc + rhs * SC_COUNT;
-  int* f = fl + rhs * FL_COUNT;
+  const double* s = fa.sc + rhs * SC_COUNT;
   __shared__ double q[SC_COUNT];  // the scalars as they were
   const double own = threadIdx.x < SC_COUNT ? s[threadIdx.x] : 0.0;
   double v[4];  // component 3: FIN_TRUE_RHO only (other stages leave it unset)
   sum_partials(partials + (int64_t)rhs * nb * (waves ? 4 : 1) * kMaxDot, nb, waves != 0, v,
                [&] { if (threadIdx.x < SC_COUNT) q[threadIdx.x] = own; });
-  if (threadIdx.x != 0) return;
-  const double stop = fa.tol * sqrt(q[SC_B2]);
-  const cx<double> rho0 = {q[SC_RHO], q[SC_RHO + 1]}, rhop0 = {q[SC_RHOP], q[SC_RHOP + 1]};
-  const cx<double> alpha0 = {q[SC_ALPHA], q[SC_ALPHA + 1]}, omega0 = {q[SC_OMEGA], q[SC_OMEGA + 1]};
-  const cx<double> one = {1.0, 0.0};
-  switch (stage) {
-    case FIN_B2: {  // |b|; the solve then runs on b / |b| (B2 becomes 1)
-      const double b2 = v[0];
-      s[SC_BNORM] = sqrt(b2);
-      s[SC_B2] = isfinite(b2) ? (b2 > 0.0 ? 1.0 : 0.0) : b2;
-      break;
-    }
-    case FIN_TRUE: {  // true FP64 residual after a (re)computation of r = b - M x
-      s[SC_RTRUE2] = v[0];
-      s[SC_MMAX] = sqrt(v[0]);
-      f[FL_CONV] = (sqrt(v[0]) <= stop) ? 1 : 0;
-      if (!isfinite(v[0])) f[FL_BREAK] = stage + 1;
-      // iteration resumes (an RHS that triggered the update was paused) unless done
-      active[rhs] = (f[FL_CONV] || f[FL_BREAK]) ? 0 : 1;
-      // FL_RU stays as the iteration set it: the host counts the update from it
-      rumask[rhs] = active[rhs];  // the residual is re-seeded only where iteration goes on
-      break;
-    }
-    case FIN_RHO: {  // after re-encoding r: rho = <r~, r^>, |r^|^2
-      s[SC_R2] = v[0];
-      s[SC_RHO] = v[1];
-      s[SC_RHO + 1] = v[2];
-      store_beta(s, {v[1], v[2]}, rhop0, alpha0, omega0);
-      break;
-    }
-    case FIN_TRUE_INIT:   // the same with a new shadow residual: a first iteration follows
-    case FIN_TRUE_RHO: {  // both, from the residual dslash that re-encoded r itself
-      s[SC_RTRUE2] = v[0];
-      s[SC_MMAX] = sqrt(v[0]);
-      f[FL_CONV] = (sqrt(v[0]) <= stop) ? 1 : 0;
-      if (!isfinite(v[0])) f[FL_BREAK] = FIN_TRUE + 1;
-      active[rhs] = (f[FL_CONV] || f[FL_BREAK]) ? 0 : 1;
-      rumask[rhs] = active[rhs];
-      if (active[rhs]) {
-        s[SC_R2] = v[1];
-        s[SC_RHO] = v[2];
-        s[SC_RHO + 1] = v[3];
-        if (stage == FIN_TRUE_INIT) {
-          s[SC_RHOP] = 1.0; s[SC_RHOP + 1] = 0.0;
-          s[SC_ALPHA] = 1.0; s[SC_ALPHA + 1] = 0.0;
-          s[SC_OMEGA] = 1.0; s[SC_OMEGA + 1] = 0.0;
-          store_beta(s, {v[2], v[3]}, one, one, one);
-        } else {
-          store_beta(s, {v[2], v[3]}, rhop0, alpha0, omega0);
-        }
-      }
-      break;
-    }
-    case FIN_BICG_INIT: {
-      s[SC_R2] = v[0];
-      s[SC_RHO] = v[1];
-      s[SC_RHO + 1] = v[2];
-      s[SC_RHOP] = 1.0; s[SC_RHOP + 1] = 0.0;
-      s[SC_ALPHA] = 1.0; s[SC_ALPHA + 1] = 0.0;
-      s[SC_OMEGA] = 1.0; s[SC_OMEGA + 1] = 0.0;
-      store_beta(s, {v[1], v[2]}, one, one, one);
-      break;
-    }
-    case FIN_BICG_ALPHA: {  // alpha = rho / <r~, v>
-      ++f[FL_ITERS];
-      const cx<double> d = {v[0], v[1]};
-      if (!(d.re * d.re + d.im * d.im > 0.0) || !isfinite(d.re) || !isfinite(d.im)) {
-        f[FL_BREAK] = stage + 1;
-        active[rhs] = 0;
-        break;
-      }
-      const cx<double> a = cdiv(rho0, d);
-      s[SC_ALPHA] = a.re;
-      s[SC_ALPHA + 1] = a.im;
-      break;
-    }
-    case FIN_BICG_OMEGA: {  // omega = <t, s> / <t, t>
-      if (v[2] == 0.0 && v[0] == 0.0 && v[1] == 0.0) {
-        // t = M_hat s = 0 means s = 0: the step already solved the system and
-        // omega is arbitrary; 1 keeps the next beta finite (r becomes 0 and a
-        // reliable update follows)
-        s[SC_OMEGA] = 1.0;
-        s[SC_OMEGA + 1] = 0.0;
-        break;
-      }
-      if (!(v[2] > 0.0) || !isfinite(v[2])) {
-        f[FL_BREAK] = stage + 1;
-        active[rhs] = 0;
-        break;
-      }
-      s[SC_OMEGA] = v[0] / v[2];
-      s[SC_OMEGA + 1] = v[1] / v[2];
-      break;
-    }
-    case FIN_BICG_ITER: {  // |r^|^2, <r~, r^>; reliable-update trigger
-      s[SC_RHOP] = rho0.re;
-      s[SC_RHOP + 1] = rho0.im;
-      s[SC_RHO] = v[1];
-      s[SC_RHO + 1] = v[2];
-      s[SC_R2] = v[0];
-      store_beta(s, {v[1], v[2]}, rho0, alpha0, omega0);
-      const double rn = sqrt(v[0]);
-      if (!isfinite(rn) || !(omega0.re * omega0.re + omega0.im * omega0.im > 0.0)) {
-        f[FL_BREAK] = stage + 1;
-        active[rhs] = 0;
-        break;
-      }
-      // reliable updates: against the largest |r^| since the last update;
-      // defect correction: against the residual the inner solve started from
-      const double mmax = fa.restart ? q[SC_MMAX] : fmax(q[SC_MMAX], rn);
-      s[SC_MMAX] = mmax;
-      const int ru = (rn < fa.delta * mmax) || (rn <= stop);
-      f[FL_RU] = ru;
-      rumask[rhs] = ru;
-      if (ru) active[rhs] = 0;  // paused until the host has run the update
-      break;
-    }
-    case FIN_CG_INIT: {  // rho = |r^|^2 of the normal-equation residual; internal target
-      s[SC_R2] = v[0];
-      s[SC_RHO] = v[0];
-      s[SC_TOLN] = fa.tol * sqrt(v[0]);
-      s[SC_MMAX] = sqrt(v[0]);
-      break;
-    }
-    case FIN_CG_ALPHA: {  // alpha = rho / |M p|^2
-      ++f[FL_ITERS];
-      if (!(v[0] > 0.0) || !isfinite(v[0])) {
-        f[FL_BREAK] = stage + 1;
-        active[rhs] = 0;
-        break;
-      }
-      s[SC_ALPHA] = rho0.re / v[0];
-      break;
-    }
-    case FIN_CG_ITER: {  // beta = |r_new|^2 / |r_old|^2; reliable-update trigger
-      const double rn = sqrt(v[0]);
-      if (!isfinite(rn)) {
-        f[FL_BREAK] = stage + 1;
-        active[rhs] = 0;
-        break;
-      }
-      s[SC_RHOP] = rho0.re;
-      s[SC_RHO] = v[0];
-      s[SC_R2] = v[0];
-      s[SC_BETA] = v[0] / rho0.re;
-      const double mmax = fa.restart ? q[SC_MMAX] : fmax(q[SC_MMAX], rn);
-      s[SC_MMAX] = mmax;
-      const int ru = (rn < fa.delta * mmax) || (rn <= q[SC_TOLN]);
-      f[FL_RU] = ru;
-      rumask[rhs] = ru;
-      if (ru) active[rhs] = 0;  // paused until the host has run the update
-      break;
-    }
-    case FIN_CG_RHO: {  // after a reliable update: new |r^|^2, beta against the old rho
-      s[SC_R2] = v[0];
-      s[SC_RHO] = v[0];
-      s[SC_BETA] = fa.restart ? 0.0 : v[0] / rhop0.re;  // defect correction: p = r^
-      s[SC_MMAX] = sqrt(v[0]);
-      break;
-    }
-    default: break;
-  }
+  if (threadIdx.x == 0) apply_stage(fa, rhs, v, q);
 }
 
 // CG stopping: at a reliable update the true residual |r| of M_hat x = b_hat is
@@ -581,9 +399,10 @@ __global__ void k_cg_tighten(int nrhs, double* sc, const int* fl, const int* mas
   if (rt > stop) s[SC_TOLN] = fmin(s[SC_TOLN], s[SC_TOLN] * stop / rt);
 }
 
-__global__ void k_init_flags(int nrhs, int* fl, int* active, int* rumask) {
+__global__ void k_init_flags(int nrhs, int* fl, int* active, int* rumask, double* sc, int counter) {
   const int rhs = blockIdx.x * blockDim.x + threadIdx.x;
   if (rhs >= nrhs) return;
+  sc[rhs * SC_COUNT + counter] = 0.0;  // FinArgs::counter: zero bits
   for (int k = 0; k < FL_COUNT; ++k) fl[rhs * FL_COUNT + k] = 0;
   active[rhs] = 1;
   rumask[rhs] = 1;
@@ -644,23 +463,23 @@ hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double
 }
 
 hipError_t blas_bicg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field rt,
-                        const double* sc, const int* mask, double* partials, hipStream_t s) {
+                        const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s) {
   return by_prec(pr, [&](auto tag) {
     using S = decltype(tag);
     by_split<S>(g, x.nrhs, [&](dim3 grid, auto split) {
       k_bicg_xr<S, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(t), fv(rt), sc,
-                                                                   mask, partials);
+                                                                   mask, partials, fa);
     });
   });
 }
 
 hipError_t blas_cg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field q,
-                      const double* sc, const int* mask, double* partials, hipStream_t s) {
+                      const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s) {
   return by_prec(pr, [&](auto tag) {
     using S = decltype(tag);
     by_split<S>(g, x.nrhs, [&](dim3 grid, auto split) {
       k_cg_xr<S, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(q), sc, mask,
-                                                                 partials);
+                                                                 partials, fa);
     });
   });
 }
@@ -724,11 +543,9 @@ hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r6
   });
 }
 
-hipError_t solver_finalize(int stage, int nrhs, int nb, int waves, const double* partials, double* sc, int* fl,
-                           int* active, int* rumask, const int* mask, double delta, double tol,
-                           int restart, hipStream_t s) {
-  k_finalize<<<nrhs, kFinBlock, 0, s>>>(stage, nb, waves, partials, sc, fl, active, rumask, mask,
-                                     FinArgs{delta, tol, restart});
+hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, const int* mask,
+                           hipStream_t s) {
+  k_finalize<<<nrhs, kFinBlock, 0, s>>>(nb, waves, partials, mask, fa);
   return hipGetLastError();
 }
 
@@ -738,8 +555,8 @@ hipError_t solver_cg_tighten(int nrhs, double* sc, const int* fl, const int* mas
   return hipGetLastError();
 }
 
-hipError_t solver_init_flags(int nrhs, int* fl, int* active, int* rumask, hipStream_t s) {
-  k_init_flags<<<(nrhs + 63) / 64, 64, 0, s>>>(nrhs, fl, active, rumask);
+hipError_t solver_init_flags(int nrhs, int* fl, int* active, int* rumask, double* sc, int counter, hipStream_t s) {
+  k_init_flags<<<(nrhs + 63) / 64, 64, 0, s>>>(nrhs, fl, active, rumask, sc, counter);
   return hipGetLastError();
 }
 

@@ -47,6 +47,7 @@ hipError_t launch_dslash_ex(const wd_gauge* g, wd_prec prec, const DslashArgs& d
     if (!form || blocks > (1 << 22)) c.split = 0;
   }
   if (d.waves && dot != DOT_NONE) *d.waves = c.split;
+  if (d.finalized) *d.finalized = 0;  // the split launch says otherwise
   // A fused dot sums each workgroup's sites into one partial record; with one
   // sub-slab and 256-thread workgroups those site sets are fixed whatever the
   // other fields are, so the reduction -- and the solver -- give the same bits

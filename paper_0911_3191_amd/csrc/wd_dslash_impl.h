@@ -35,7 +35,7 @@
 #include <algorithm>
 
 #include "wd_device.h"
-#include "wd_reduce.h"
+#include "wd_finalize.h"
 
 namespace wd {
 
@@ -1071,6 +1071,7 @@ __device__ __forceinline__ void hop_pair(Spinor<typename S::real> (&acc)[NR], co
 struct EncView {
   FieldView rh, xh, rt;
   int set_rt;
+  FinArgs fin;  // WAVE kernels: the finalize stage that the last wavefront runs (stage < 0: none)
 };
 
 // The epilogue fuses its products explicitly.  Left to the compiler, x + a*acc
@@ -1101,9 +1102,13 @@ __device__ __forceinline__ void acc_norm(T& nn, const cx<R>& u) {
 // WAVE: one wavefront works alone; its x and y come in xw, yw and it writes
 // wave records (see wave_sum_store).
 template <int N, bool WAVE>
-__device__ __forceinline__ void sum_store(double (&d)[N], double* out) {
-  if constexpr (WAVE) wave_sum_store<N>(d, out);
-  else block_sum_store<N>(d, out);
+__device__ __forceinline__ void sum_store(double (&d)[N], double* rec, int pid, int nb, int r, const FinArgs& fa) {
+  if constexpr (WAVE) {
+    if (fa.stage >= 0) wave_sum_finalize<N>(d, rec, pid, nb, r, fa);
+    else wave_sum_store<N>(d, rec + (int64_t)pid * kMaxDot);
+  } else {
+    block_sum_store<N>(d, rec + (int64_t)pid * kMaxDot);
+  }
 }
 
 template <class S, bool XPAY, int DOT, class S2, bool WAVE = false>
@@ -1161,7 +1166,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
       d[0] = n2;
     }
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
-    sum_store<1, WAVE>(d, partials + ((int64_t)r * nb + pid) * kMaxDot);
+    sum_store<1, WAVE>(d, partials + (int64_t)r * nb * kMaxDot, pid, nb, r, enc.fin);
   }
   if constexpr (DOT == DOT_RES_ENC) {
     using R2 = typename S2::real;
@@ -1200,11 +1205,11 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
       d[3] = im;
     }
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
-    sum_store<4, WAVE>(d, partials + ((int64_t)r * nb + pid) * kMaxDot);
+    sum_store<4, WAVE>(d, partials + (int64_t)r * nb * kMaxDot, pid, nb, r, enc.fin);
   }
   if constexpr (DOT != DOT_NONE && DOT != DOT_RES_ENC && DOT != DOT_ENC) {
     const int nb = (g.slab ? 8 : 1) * g.site_blocks;
-    double* part = partials + ((int64_t)r * nb + pid) * kMaxDot;
+    double* part = partials + (int64_t)r * nb * kMaxDot;
     if constexpr (DOT == DOT_YO) {
       double d[2] = {0.0, 0.0};
       if (valid) {
@@ -1219,7 +1224,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         d[0] = re;
         d[1] = im;
       }
-      sum_store<2, WAVE>(d, part);
+      sum_store<2, WAVE>(d, part, pid, nb, r, enc.fin);
     } else if constexpr (DOT == DOT_OX) {
       double d[3] = {0.0, 0.0, 0.0};
       if (valid) {
@@ -1235,7 +1240,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         d[1] = im;
         d[2] = nn;
       }
-      sum_store<3, WAVE>(d, part);
+      sum_store<3, WAVE>(d, part, pid, nb, r, enc.fin);
     } else {
       double d[1] = {0.0};
       if (valid) {
@@ -1246,7 +1251,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
           for (int c = 0; c < 3; ++c) acc_norm(nn, acc.v[s][c]);
         d[0] = nn;
       }
-      sum_store<1, WAVE>(d, part);
+      sum_store<1, WAVE>(d, part, pid, nb, r, enc.fin);
     }
   }
 }
@@ -1711,7 +1716,7 @@ static void launch_nr(const wd_gauge* gg, const DslashArgs& d, const LaunchCfg& 
   using R = typename S::real;
   const R ar = static_cast<R>(d.a);
   const int dot = d.xpay ? d.dot : DOT_NONE;
-  const EncView ev{fview(d.enc_rh), fview(d.enc_xh), fview(d.enc_rt), d.enc_set_rt};
+  const EncView ev{fview(d.enc_rh), fview(d.enc_xh), fview(d.enc_rt), d.enc_set_rt, FinArgs{-1}};
   size_t lds = lds_for(c.wgs);
   if constexpr (LDS) lds = std::max(lds, lds_stage_bytes(g, NR));
   if (d.dagger) {
@@ -1752,7 +1757,7 @@ static void launch_rloop_dag(const DslashArgs& d, unsigned grid, int block, size
   FieldView fo = fview(d.out), fi = fview(d.in), fx = fview(d.xpay), fy = fview(d.y);
   const float ar = static_cast<float>(d.a);
   const int dot = d.xpay ? d.dot : DOT_NONE;
-  const EncView ev{fview(d.enc_rh), fview(d.enc_xh), fview(d.enc_rt), d.enc_set_rt};
+  const EncView ev{fview(d.enc_rh), fview(d.enc_xh), fview(d.enc_rt), d.enc_set_rt, FinArgs{-1}};
   const int* sel = d.rhs_map ? d.rhs_map : d.active;
   if (d.dagger) {
     if (d.xpay) launch_rloop_dot<true, true, BASIS, LDS>(dot, grid, block, lds, s, g, links, fo, fi, fx, fy, ar, d.out_parity, sel, d.partials, ev);

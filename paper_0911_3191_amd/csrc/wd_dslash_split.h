@@ -388,7 +388,11 @@ static void launch_split_recon(const wd_gauge* gg, const DslashArgs& d, hipStrea
   const FieldView fo = fview(d.out), fi = fview(d.in), fx = fview(d.xpay), fy = fview(d.y);
   const auto ar = static_cast<typename S::real>(d.a);
   const int dot = d.xpay ? d.dot : DOT_NONE;
-  const EncView ev{fview(d.enc_rh), fview(d.enc_xh), fview(d.enc_rt), d.enc_set_rt};
+  EncView ev{fview(d.enc_rh), fview(d.enc_xh), fview(d.enc_rt), d.enc_set_rt, FinArgs{-1}};
+  if (d.finalized) {
+    *d.finalized = dot != DOT_NONE && d.fin.stage >= 0 && (g.slab ? 8 : 1) * g.site_blocks <= kFusedRecords;
+    if (*d.finalized) ev.fin = d.fin;
+  }
   const int* sel = d.rhs_map ? d.rhs_map : d.active;
   if (d.dagger) {
     if (d.xpay) launch_split_dot<S, true, true, RECON, BASIS, HPW>(dot, grid, s, g, links, fo, fi, fx, fy, ar, d.out_parity, sel, d.wave_partials, ev, d.enc_prec);

@@ -61,6 +61,50 @@ struct wd_gauge {
 
 namespace wd {
 
+// ---- solver state on the device --------------------------------------------------
+// Per-RHS FP64 scalars (complex ones take two slots: re, im).
+enum ScalarSlot {
+  SC_RHO = 0,      // rho = <r~, r^> (BiCGstab, complex) or |r^|^2 (CG)
+  SC_RHOP = 2,     // previous rho
+  SC_ALPHA = 4,    // alpha (complex for BiCGstab)
+  SC_OMEGA = 6,    // omega (BiCGstab)
+  SC_R2 = 8,       // |r^|^2 of the iterated residual
+  SC_RTRUE2 = 9,   // |b_hat - M_hat x|^2 at the last reliable update (FP64)
+  SC_MMAX = 10,    // max |r^| since the last reliable update (Algorithm 2's M)
+  SC_B2 = 11,      // |b|^2 of the full-lattice source
+  SC_TOLN = 12,    // CG: target on the normal-equation residual
+  SC_BETA = 13,    // beta (BiCGstab, complex: the imaginary part in SC_BETA_IM)
+  SC_BNORM = 14,   // |b| of the caller's source (the solve runs on b / |b|)
+  SC_BETA_IM = 15,
+  SC_COUNT = 16
+};
+// FL_ITERS counts the inner iterations an RHS has started, on the device, so
+// that several iterations can run between two reads of the flags by the host.
+enum FlagSlot { FL_RU = 0, FL_BREAK = 1, FL_CONV = 2, FL_ITERS = 3, FL_COUNT = 4 };
+enum FinStage {
+  FIN_B2, FIN_TRUE, FIN_RHO, FIN_BICG_INIT, FIN_BICG_ALPHA, FIN_BICG_OMEGA,
+  FIN_BICG_ITER, FIN_CG_INIT, FIN_CG_ALPHA, FIN_CG_ITER, FIN_CG_RHO,
+  FIN_TRUE_RHO,  // FIN_TRUE on v[0], then FIN_RHO on v[1..3] where iteration goes on
+  FIN_TRUE_INIT  // FIN_TRUE on v[0], then FIN_BICG_INIT on v[1..3] where iteration goes on
+};
+// A finalize stage: what it does and where the scalars live.  restart = 1
+// (defect correction): the update trigger compares |r^| with the residual the
+// inner solve started from, and CG restarts with beta = 0.
+struct FinArgs {
+  int stage;     // FinStage; -1: none (the kernel only writes its records)
+  double* sc;    // [rhs][SC_COUNT]
+  int* fl;       // [rhs][FL_COUNT]
+  int* active;
+  int* rumask;
+  double delta;  // reliable-update trigger (defect correction: inner tolerance)
+  double tol;    // target relative residual
+  int restart;   // 1: defect correction (Algorithm 1), 0: reliable updates (Algorithm 2)
+  int counter;   // scalar slot whose bits count the workgroups of a fused finalize
+};
+// Most records per RHS that the last workgroup of their kernel sums itself
+// (the figures are in wd_finalize.h).
+constexpr int kFusedRecords = 128;
+
 // ---- launchers (defined in the .hip files; all asynchronous on `s`) -------------
 constexpr int kMaxDotHost = 4;  // doubles per partial record
 // DOT_RES (FP64 only): out = y - (xpay + a D in), the residual of a reliable
@@ -95,6 +139,10 @@ struct DslashArgs {
   // launch says whether it wrote those (1) or `partials` (0).
   double* wave_partials = nullptr;
   int* waves = nullptr;
+  // The finalize stage that follows, which a launch with few enough wave
+  // records runs itself (`finalized` then reads 1).
+  FinArgs fin{-1};
+  int* finalized = nullptr;
   const int* active = nullptr;  // device mask [nrhs]: RHS with 0 are skipped
   // Device list of n_map RHS indices (distinct, < out.nrhs): only those are
   // processed, packed into as few RHS groups as they fill (replaces `active`).
@@ -178,33 +226,6 @@ hipError_t launch_spinor_encode_both(const Geom& g, Field fe, Field fo, const do
 hipError_t launch_spinor_decode_both(const Geom& g, double* canon, Field fe, Field fo, hipStream_t s,
                                      int basis, const double* sc = nullptr, int scale = 0);
 
-// ---- solver state on the device --------------------------------------------------
-// Per-RHS FP64 scalars (complex ones take two slots: re, im).
-enum ScalarSlot {
-  SC_RHO = 0,      // rho = <r~, r^> (BiCGstab, complex) or |r^|^2 (CG)
-  SC_RHOP = 2,     // previous rho
-  SC_ALPHA = 4,    // alpha (complex for BiCGstab)
-  SC_OMEGA = 6,    // omega (BiCGstab)
-  SC_R2 = 8,       // |r^|^2 of the iterated residual
-  SC_RTRUE2 = 9,   // |b_hat - M_hat x|^2 at the last reliable update (FP64)
-  SC_MMAX = 10,    // max |r^| since the last reliable update (Algorithm 2's M)
-  SC_B2 = 11,      // |b|^2 of the full-lattice source
-  SC_TOLN = 12,    // CG: target on the normal-equation residual
-  SC_BETA = 13,    // beta (BiCGstab, complex: the imaginary part in SC_BETA_IM)
-  SC_BNORM = 14,   // |b| of the caller's source (the solve runs on b / |b|)
-  SC_BETA_IM = 15,
-  SC_COUNT = 16
-};
-// FL_ITERS counts the inner iterations an RHS has started, on the device, so
-// that several iterations can run between two reads of the flags by the host.
-enum FlagSlot { FL_RU = 0, FL_BREAK = 1, FL_CONV = 2, FL_ITERS = 3, FL_COUNT = 4 };
-enum FinStage {
-  FIN_B2, FIN_TRUE, FIN_RHO, FIN_BICG_INIT, FIN_BICG_ALPHA, FIN_BICG_OMEGA,
-  FIN_BICG_ITER, FIN_CG_INIT, FIN_CG_ALPHA, FIN_CG_ITER, FIN_CG_RHO,
-  FIN_TRUE_RHO,  // FIN_TRUE on v[0], then FIN_RHO on v[1..3] where iteration goes on
-  FIN_TRUE_INIT  // FIN_TRUE on v[0], then FIN_BICG_INIT on v[1..3] where iteration goes on
-};
-
 hipError_t blas_bicg_p(const Geom& g, wd_prec pr, Field p, Field r, Field v, const double* sc,
                        const int* mask, hipStream_t s);
 hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double* sc,
@@ -213,9 +234,9 @@ hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double
 // times those of the other kernels).
 int blas_dot_records(const Geom& g, wd_prec p);
 hipError_t blas_bicg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field rt,
-                        const double* sc, const int* mask, double* partials, hipStream_t s);
+                        const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s);
 hipError_t blas_cg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field q,
-                      const double* sc, const int* mask, double* partials, hipStream_t s);
+                      const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s);
 hipError_t blas_cg_p(const Geom& g, wd_prec pr, Field p, Field r, const double* sc,
                      const int* mask, hipStream_t s);
 hipError_t blas_convert(const Geom& g, wd_prec dst_prec, Field dst, wd_prec src_prec, Field src,
@@ -231,15 +252,13 @@ hipError_t blas_canon_norm2(const Geom& g, const double* canon, int nrhs, double
 // writes rt <- enc(r64) first (the same bits as rh).
 hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r64, const Field* rt,
                          const int* mask, double* partials, hipStream_t s, bool set_rt = false);
-// restart = 1 (defect correction): the update trigger compares |r^| with the
-// residual the inner solve started from, and CG restarts with beta = 0.
-// waves: the records are wave records, four to each of the nb (DslashArgs::waves).
-hipError_t solver_finalize(int stage, int nrhs, int nb, int waves, const double* partials, double* sc, int* fl,
-                           int* active, int* rumask, const int* mask, double delta, double tol,
-                           int restart, hipStream_t s);
+// fa.stage on the nb records per RHS of a launch (waves: wave records, four to
+// each, see DslashArgs::waves).
+hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, const int* mask,
+                           hipStream_t s);
 hipError_t solver_cg_tighten(int nrhs, double* sc, const int* fl, const int* mask, double tol,
                              hipStream_t s);
-hipError_t solver_init_flags(int nrhs, int* fl, int* active, int* rumask, hipStream_t s);
+hipError_t solver_init_flags(int nrhs, int* fl, int* active, int* rumask, double* sc, int counter, hipStream_t s);
 
 // ---- two-phase stepping (wd_solver.cpp), used by the serving scheduler ---------------
 bool solver_finished(wd_solver* h);

@@ -70,6 +70,7 @@ struct wd_solver {
   int nrhs, nb, nb_dslash;  // partial records per RHS: BLAS-1 kernels, fused-dot dslash
   int waves;                // the last fused-dot dslash wrote wave records into wave_records
   double* wave_records;
+  int finalized;            // ... and has run its finalize stage
   wd::Field bhat, x, r, rn, to64;
   wd::Field rh, rt, p, v, t, xh, to;  // CG uses v as q and t as w; rt unused
   double* partials;
@@ -94,14 +95,26 @@ struct wd_solver {
 
 namespace wd {
 
+// The scalar slot that counts workgroups (FinArgs::counter): one that the
+// solver does not use otherwise.
+static int counter_slot(int kind) { return kind == WD_SOLVER_CG ? SC_OMEGA : SC_TOLN; }
+
+static FinArgs fin_args(wd_solver* h, int stage) {
+  return FinArgs{stage, h->sc, h->fl, h->active, h->rumask, h->prm.delta, h->prm.tol, h->prm.restart,
+                 counter_slot(h->kind)};
+}
+
 // Room for the wave records of a fused dot: whichever odd temporary the launch
 // does not use (the FP64 one is free while the inner solver iterates, the
-// inner one during prepare and the reliable updates).
-static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d) {
+// inner one during prepare and the reliable updates).  stage: the finalize
+// stage that the caller runs next with fin().
+static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d, int stage) {
   const bool hi = d.in.ptr == h->to64.ptr || d.out.ptr == h->to64.ptr || (d.xpay && d.xpay->ptr == h->to64.ptr);
   h->wave_records = reinterpret_cast<double*>(hi ? h->to.ptr : h->to64.ptr);
   d.wave_partials = h->wave_records;
   d.waves = &h->waves;
+  d.fin = fin_args(h, stage);
+  d.finalized = &h->finalized;
   return launch_dslash_ex(h->g, prec, d, h->s);
 }
 
@@ -109,7 +122,7 @@ static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d) {
 // same set as mask), packed into as few RHS groups as they fill.
 static hipError_t dslash_into(wd_solver* h, wd_prec prec, const Field& out, const Field& in,
                               int parity, int dagger, const Field* xpay, double a, int dot,
-                              const Field* y, const int* mask, int n_map = 0) {
+                              const Field* y, const int* mask, int n_map = 0, int stage = -1) {
   DslashArgs d;
   d.out = out;
   d.in = in;
@@ -126,16 +139,16 @@ static hipError_t dslash_into(wd_solver* h, wd_prec prec, const Field& out, cons
     d.rhs_map = h->rumap;
     d.n_map = n_map;
   }
-  return launch_dot(h, prec, d);
+  return launch_dot(h, prec, d, stage);
 }
 
 // out_e = in_e - kappa^2 D_eo D_oe in_e (dagger: the adjoint), optional fused dot.
 static hipError_t mhat_into(wd_solver* h, wd_prec prec, const Field& out, const Field& in,
                             const Field& tmp_odd, int dagger, int dot, const Field* y,
-                            const int* mask, int n_map = 0) {
+                            const int* mask, int n_map = 0, int stage = -1) {
   hipError_t e = dslash_into(h, prec, tmp_odd, in, 1, dagger, nullptr, 0.0, DOT_NONE, nullptr, mask, n_map);
   if (e != hipSuccess) return e;
-  return dslash_into(h, prec, out, tmp_odd, 0, dagger, &in, -h->kappa * h->kappa, dot, y, mask, n_map);
+  return dslash_into(h, prec, out, tmp_odd, 0, dagger, &in, -h->kappa * h->kappa, dot, y, mask, n_map, stage);
 }
 
 // Records of the iteration's x/r update: more than h->partials has room for
@@ -144,16 +157,32 @@ static double* xr_records(wd_solver* h) {
   return blas_dot_records(h->geom, h->prm.inner) <= h->nb ? h->partials : reinterpret_cast<double*>(h->to64.ptr);
 }
 
-// after_dslash: the partial records come from a dslash with a fused dot
-// (its record count per RHS), else from a BLAS-1 kernel.
+// Finalize stage on the records of the last launch, unless that launch ran it
+// itself.  after_dslash: they come from a dslash with a fused dot, else from a
+// BLAS-1 kernel.
 static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash) {
-  const int waves = after_dslash ? h->waves : 0;
-  if (stage == FIN_BICG_ITER || stage == FIN_CG_ITER)  // after the x/r update
-    return solver_finalize(stage, h->nrhs, blas_dot_records(h->geom, h->prm.inner), 0, xr_records(h), h->sc, h->fl,
-                           h->active, h->rumask, mask, h->prm.delta, h->prm.tol, h->prm.restart, h->s);
-  return solver_finalize(stage, h->nrhs, after_dslash ? h->nb_dslash : h->nb, waves,
-                         waves ? h->wave_records : h->partials, h->sc, h->fl, h->active, h->rumask, mask, h->prm.delta, h->prm.tol, h->prm.restart,
-                         h->s);
+  if (after_dslash) {
+    if (h->finalized) return hipSuccess;
+    return solver_finalize(fin_args(h, stage), h->nrhs, h->nb_dslash, h->waves,
+                           h->waves ? h->wave_records : h->partials, mask, h->s);
+  }
+  return solver_finalize(fin_args(h, stage), h->nrhs, h->nb, 0, h->partials, mask, h->s);
+}
+
+// The iteration's x/r update and its finalize stage, in one launch where its
+// records are few.
+static hipError_t update_xr(wd_solver* h, const int* act) {
+  const wd_prec P = h->prm.inner;
+  const int records = blas_dot_records(h->geom, P);
+  const bool cg = h->kind == WD_SOLVER_CG;
+  const FinArgs fa = fin_args(h, cg ? FIN_CG_ITER : FIN_BICG_ITER);
+  FinArgs in_kernel = fa;
+  if (records > kFusedRecords) in_kernel.stage = -1;
+  hipError_t e = cg ? blas_cg_xr(h->geom, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), in_kernel, h->s)
+                    : blas_bicg_xr(h->geom, P, h->xh, h->rh, h->p, h->t, h->rt, h->sc, act, xr_records(h), in_kernel,
+                                   h->s);
+  if (e != hipSuccess || in_kernel.stage >= 0) return e;
+  return solver_finalize(fa, h->nrhs, records, 0, xr_records(h), act, h->s);
 }
 
 #define WD_TRY(expr)                         \
@@ -207,20 +236,18 @@ static hipError_t iteration_body(wd_solver* h) {
   const int* act = h->active;
   if (h->kind == WD_SOLVER_BICGSTAB) {
     WD_TRY(blas_bicg_p(g, P, h->p, h->rh, h->v, h->sc, act, h->s));
-    WD_TRY(mhat_into(h, P, h->v, h->p, h->to, 0, DOT_YO, &h->rt, act));  // v = M p, <r~, v>
+    WD_TRY(mhat_into(h, P, h->v, h->p, h->to, 0, DOT_YO, &h->rt, act, 0, FIN_BICG_ALPHA));  // v = M p, <r~, v>
     WD_TRY(fin(h, FIN_BICG_ALPHA, act, true));
     WD_TRY(blas_bicg_s(g, P, h->rh, h->v, h->sc, act, h->s));           // s = r - alpha v
-    WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, nullptr, act));  // t = M s, <t,s>, |t|^2
+    WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, nullptr, act, 0, FIN_BICG_OMEGA));  // t = M s, <t,s>, |t|^2
     WD_TRY(fin(h, FIN_BICG_OMEGA, act, true));
-    WD_TRY(blas_bicg_xr(g, P, h->xh, h->rh, h->p, h->t, h->rt, h->sc, act, xr_records(h), h->s));
-    WD_TRY(fin(h, FIN_BICG_ITER, act, false));
+    WD_TRY(update_xr(h, act));
   } else {
     // w = M p (|w|^2), q = M^dag w, x^ += alpha p, r^ -= alpha q
-    WD_TRY(mhat_into(h, P, h->t, h->p, h->to, 0, DOT_OO, nullptr, act));
+    WD_TRY(mhat_into(h, P, h->t, h->p, h->to, 0, DOT_OO, nullptr, act, 0, FIN_CG_ALPHA));
     WD_TRY(fin(h, FIN_CG_ALPHA, act, true));
     WD_TRY(mhat_into(h, P, h->v, h->t, h->to, 1, DOT_NONE, nullptr, act));
-    WD_TRY(blas_cg_xr(g, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), h->s));
-    WD_TRY(fin(h, FIN_CG_ITER, act, false));
+    WD_TRY(update_xr(h, act));
     // p = r^ + beta p where iteration goes on; an RHS that triggered a
     // reliable update is paused and takes this step after the update
     WD_TRY(blas_cg_p(g, P, h->p, h->rh, h->sc, act, h->s));
@@ -263,8 +290,9 @@ static hipError_t true_residual(wd_solver* h, const int* mask, int n_map = 0, bo
   d.enc_xh = &h->xh;
   d.enc_rt = &h->rt;
   d.enc_set_rt = h->prm.restart;
-  WD_TRY(launch_dot(h, WD_FP64, d));
-  WD_TRY(fin(h, !reencode ? FIN_TRUE : (h->prm.restart ? FIN_TRUE_INIT : FIN_TRUE_RHO), mask, true));
+  const int stage = !reencode ? FIN_TRUE : (h->prm.restart ? FIN_TRUE_INIT : FIN_TRUE_RHO);
+  WD_TRY(launch_dot(h, WD_FP64, d, stage));
+  WD_TRY(fin(h, stage, mask, true));
   if (reencode && h->prm.restart) {  // p = v = 0 where the restarted solve goes on
     WD_TRY(blas_zero(h->geom, h->prm.inner, h->p, h->rumask, h->s));
     WD_TRY(blas_zero(h->geom, h->prm.inner, h->v, h->rumask, h->s));
@@ -318,7 +346,7 @@ static hipError_t reseed(wd_solver* h, bool first, const Field& r64, int n_map =
         d.rhs_map = h->rumap;
         d.n_map = n_map;
       }
-      WD_TRY(launch_dot(h, WD_FP64, d));
+      WD_TRY(launch_dot(h, WD_FP64, d, first ? FIN_CG_INIT : FIN_CG_RHO));
     }
     WD_TRY(fin(h, first ? FIN_CG_INIT : FIN_CG_RHO, h->rumask, fused));
     if (first) WD_TRY(blas_convert(g, P, h->p, P, h->rh, h->rumask, h->s));  // p = r^
@@ -371,7 +399,7 @@ static hipError_t read_flags(wd_solver* h) {
 static hipError_t prepare(wd_solver* h) {
   const Geom& g = h->geom;
   const int n = h->nrhs;
-  WD_TRY(solver_init_flags(n, h->fl, h->active, h->rumask, h->s));
+  WD_TRY(solver_init_flags(n, h->fl, h->active, h->rumask, h->sc, counter_slot(h->kind), h->s));
   // |b| of the caller's source, then the solve runs on b / |b| (a unit source
   // per RHS; x is scaled back when it is decoded)
   WD_TRY(blas_canon_norm2(g, h->b_in, h->nrhs, h->partials, h->s));
@@ -384,7 +412,7 @@ static hipError_t prepare(wd_solver* h) {
   // b_hat = b_e + kappa D_eo b_o, with |b_hat|^2 from the same launch.  x = 0,
   // so r = b_hat - M_hat x is b_hat exactly: the convergence test and the
   // first inner residual read b_hat (no further dslash needed)
-  WD_TRY(dslash_into(h, WD_FP64, h->bhat, h->r, 0, 0, &h->to64, h->kappa, DOT_OO, nullptr, nullptr));
+  WD_TRY(dslash_into(h, WD_FP64, h->bhat, h->r, 0, 0, &h->to64, h->kappa, DOT_OO, nullptr, nullptr, 0, FIN_TRUE));
   WD_TRY(fin(h, FIN_TRUE, nullptr, true));
   WD_TRY(blas_zero(g, WD_FP64, h->x, nullptr, h->s));
   WD_TRY(blas_zero(g, h->prm.inner, h->p, nullptr, h->s));
