@@ -307,6 +307,10 @@ static bool split_pays(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
   const int64_t site = is_half(prec) ? 52 : (prec == WD_FP64 ? 192 : 96);
   const int64_t bytes = Vh * (8 * link_bytes(prec, g->recon) + 2 * n * site);
   if (is_half(prec)) return n == 1 ? bytes <= (200 << 20) : Vh * n <= (1 << 17);
+  // the residual forms end in long FP64 epilogues, which the split kernel's one
+  // finishing wavefront takes alone: 8^4 11.0 / 7.1, 24^3x32 64.8 / 74.3
+  const bool residual = d.xpay && (d.dot == DOT_RES || d.dot == DOT_RES_ENC || d.dot == DOT_ENC);
+  if (residual && Vh * n > (1 << 16)) return false;
   return bytes <= (prec == WD_FP64 ? (256 << 20) : (300 << 20));
 }
 
