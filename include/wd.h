@@ -287,7 +287,8 @@ typedef struct {
                           confirm convergence) */
   int32_t nrhs;        /* right-hand sides solved together, 1..64 (one multi-RHS dslash per hop) */
   int32_t use_graph;   /* 1: the iteration body is captured once as a hipGraph and replayed
-                          (needs a non-NULL stream) */
+                          (needs a non-NULL stream); a solve shorter than 12 batches of
+                          check_every iterations launches them directly */
   int32_t check_every; /* inner iterations launched (and, with use_graph, captured in one
                           graph) between two reads of the per-RHS flags by the host, 0..64
                           (0 and 1: every iteration).  An RHS that triggers a reliable

@@ -141,9 +141,9 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
       // defect correction: against the residual the inner solve started from
       const double mmax = fa.restart ? q[SC_MMAX] : fmax(q[SC_MMAX], rn);
       s[SC_MMAX] = mmax;
-      const int ru = (rn < fa.delta * mmax) || (rn <= stop);
+      const int ru = rn <= stop ? 2 : (rn < fa.delta * mmax ? 1 : 0);
       f[FL_RU] = ru;
-      rumask[rhs] = ru;
+      rumask[rhs] = ru != 0;
       if (ru) active[rhs] = 0;  // paused until the host has run the update
       break;
     }
@@ -177,9 +177,9 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
       s[SC_BETA] = v[0] / rho0.re;
       const double mmax = fa.restart ? q[SC_MMAX] : fmax(q[SC_MMAX], rn);
       s[SC_MMAX] = mmax;
-      const int ru = (rn < fa.delta * mmax) || (rn <= q[SC_TOLN]);
+      const int ru = rn <= q[SC_TOLN] ? 2 : (rn < fa.delta * mmax ? 1 : 0);
       f[FL_RU] = ru;
-      rumask[rhs] = ru;
+      rumask[rhs] = ru != 0;
       if (ru) active[rhs] = 0;  // paused until the host has run the update
       break;
     }

@@ -80,6 +80,7 @@ enum ScalarSlot {
 };
 // FL_ITERS counts the inner iterations an RHS has started, on the device, so
 // that several iterations can run between two reads of the flags by the host.
+// FL_RU: 0, 1 (the residual has dropped by delta) or 2 (it may have converged).
 enum FlagSlot { FL_RU = 0, FL_BREAK = 1, FL_CONV = 2, FL_ITERS = 3, FL_COUNT = 4 };
 enum FinStage {
   FIN_B2, FIN_TRUE, FIN_RHO, FIN_BICG_INIT, FIN_BICG_ALPHA, FIN_BICG_OMEGA,

@@ -81,11 +81,12 @@ struct wd_solver {
   int* rumap;      // the RHS of a reliable update, listed (device)
   int* h_fl;       // pinned host copy of the flags
   int* h_map;      // pinned host staging of rumap (after the flags in the same buffer)
-  double* h_sc;    // pinned host copy of the scalars
+  double* h_sc;    // pinned host copy of the scalars (the start of the same buffer)
   std::vector<int> iters, rus, status, done_rhs;
   std::string note;  // breakdown details for wd_last_error
   int per_check;     // inner iterations launched between two reads of the flags
   int loops;
+  int batches;       // batches of per_check iterations launched
   bool finished;
   hipGraph_t graph;
   hipGraphExec_t gexec;
@@ -390,9 +391,11 @@ static void note_breakdown(wd_solver* h, int k) {
   h->note += buf;
 }
 
-static hipError_t read_flags(wd_solver* h) {
+// Waits for the stream and reads the flags, with the scalars where asked.
+static hipError_t read_flags(wd_solver* h, bool scalars = true) {
   WD_TRY(hipMemcpyAsync(h->h_fl, h->fl, sizeof(int) * FL_COUNT * h->nrhs, hipMemcpyDeviceToHost, h->s));
-  WD_TRY(hipMemcpyAsync(h->h_sc, h->sc, sizeof(double) * SC_COUNT * h->nrhs, hipMemcpyDeviceToHost, h->s));
+  if (scalars)
+    WD_TRY(hipMemcpyAsync(h->h_sc, h->sc, sizeof(double) * SC_COUNT * h->nrhs, hipMemcpyDeviceToHost, h->s));
   return hipStreamSynchronize(h->s);
 }
 
@@ -423,7 +426,7 @@ static hipError_t prepare(wd_solver* h) {
 
 // x_o = b_o + kappa D_oe x_e for the unit source (b_o / |b| from r where the
 // solve kept it, else encoded again into to64), then both parities into the
-// caller's x, times |b| and back in the DeGrand-Rossi basis.
+// caller's x, times |b| and back in the DeGrand-Rossi basis.  Asynchronous.
 static hipError_t reconstruct(wd_solver* h) {
   const Geom& g = h->geom;
   const Field* bo = &h->r;
@@ -432,8 +435,7 @@ static hipError_t reconstruct(wd_solver* h) {
     bo = &h->to64;
   }
   WD_TRY(dslash_into(h, WD_FP64, h->to64, h->x, 1, 0, bo, h->kappa, DOT_NONE, nullptr, nullptr));
-  WD_TRY(launch_spinor_decode_both(g, h->x_out, h->x, h->to64, h->s, kBasisUK, h->sc, 2));
-  return hipStreamSynchronize(h->s);
+  return launch_spinor_decode_both(g, h->x_out, h->x, h->to64, h->s, kBasisUK, h->sc, 2);
 }
 
 static wd_status hip_fail(hipError_t e, const char* where) {
@@ -544,28 +546,26 @@ wd_status wd_solver_begin(int32_t solver, const wd_gauge* g, double kappa, doubl
   h->per_check = prm->check_every > 1 ? prm->check_every : 1;
   h->loops = 0;
   h->t0 = std::chrono::steady_clock::now();
-  hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->h_fl), sizeof(int) * (FL_COUNT + 1) * h->nrhs);
-  h->h_map = h->h_fl + FL_COUNT * h->nrhs;
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void**>(&h->h_sc), sizeof(double) * SC_COUNT * h->nrhs);
+  hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->h_sc),
+                               (sizeof(double) * SC_COUNT + sizeof(int) * (FL_COUNT + 1)) * h->nrhs);
   if (e != hipSuccess) {
     delete h;
     return hip_fail(e, "pinned host buffer");
   }
+  h->h_fl = reinterpret_cast<int*>(h->h_sc + SC_COUNT * h->nrhs);
+  h->h_map = h->h_fl + FL_COUNT * h->nrhs;
   e = prepare(h);  // its FP64 dslash launches pick their own launch shape
   // pick the inner-precision launch shapes of every form an iteration uses
   // before any graph capture
   if (e == hipSuccess) e = pretune_inner(h);
   if (e == hipSuccess) e = read_flags(h);
   if (e != hipSuccess) {
-    (void)hipHostFree(h->h_fl);
     (void)hipHostFree(h->h_sc);
     delete h;
     return hip_fail(e, "solver prepare");
   }
   for (int k = 0; k < h->nrhs; ++k) {
     if (!std::isfinite(h->h_sc[k * SC_COUNT + SC_B2])) {
-      (void)hipHostFree(h->h_fl);
       (void)hipHostFree(h->h_sc);
       delete h;
       return fail(WD_EINVAL, "source contains NaN or Inf");
@@ -582,6 +582,27 @@ wd_status wd_solver_begin(int32_t solver, const wd_gauge* g, double kappa, doubl
 }  // extern "C"
 
 namespace wd {
+
+// Iterations so far and the right-hand sides that have converged or broken
+// down, from the flags read last.
+static hipError_t account(wd_solver* h) {
+  bool scalars = false;  // a breakdown note quotes them
+  for (int k = 0; k < h->nrhs; ++k) {
+    if (h->done_rhs[k]) continue;
+    h->iters[k] = h->h_fl[k * FL_COUNT + FL_ITERS] + h->rus[k];
+    if (h->h_fl[k * FL_COUNT + FL_BREAK]) {
+      if (!scalars) WD_TRY(read_flags(h));
+      scalars = true;
+      h->done_rhs[k] = 1;
+      h->status[k] = WD_EBREAKDOWN;
+      note_breakdown(h, k);
+    } else if (h->h_fl[k * FL_COUNT + FL_CONV]) {
+      h->done_rhs[k] = 1;
+      h->status[k] = WD_OK;
+    }
+  }
+  return hipSuccess;
+}
 
 bool solver_finished(wd_solver* h) {
   if (h->finished) return true;
@@ -601,9 +622,17 @@ static hipError_t issue_body(wd_solver* h) {
   return hipSuccess;
 }
 
+// With use_graph the body is captured once the solve has run kGraphAfter
+// batches: capture, instantiation and destruction cost the host about 130 us,
+// and a replay saves it about 11 us of a batch of four iterations (8^4), so a
+// shorter solve launches its batches directly.  Captured from the first batch
+// / after 12: 8^4 FP64 BiCGstab 1056 / 988 us, 24^3x32 binary16 6334 / 6010,
+// level on 12 right-hand sides and on eight solves at once.
+constexpr int kGraphAfter = 12;
+
 hipError_t solver_issue(wd_solver* h) {
   hipError_t e = hipSuccess;
-  if (h->prm.use_graph && h->s) {
+  if (h->prm.use_graph && h->s && h->batches >= kGraphAfter) {
     if (!h->graph_ready) {
       e = hipStreamBeginCapture(h->s, hipStreamCaptureModeRelaxed);
       if (e == hipSuccess) {
@@ -618,63 +647,48 @@ hipError_t solver_issue(wd_solver* h) {
   } else {
     e = issue_body(h);
   }
+  ++h->batches;
   // only the flags come back every iteration; the scalars are read when a
-  // breakdown is reported, at a reliable update and at the end
+  // breakdown is reported and at the end
   if (e == hipSuccess)
     e = hipMemcpyAsync(h->h_fl, h->fl, sizeof(int) * FL_COUNT * h->nrhs, hipMemcpyDeviceToHost, h->s);
   return e;
 }
 
-// Wait for the issued iterations, account for them, and run the reliable
+// Wait for the issued iterations, account for them, and launch the reliable
 // update of the RHS that triggered one (CG: then their search-direction
 // update).  Iterations are counted on the device (FL_ITERS); a reliable
-// update counts as one more (k + l).
+// update counts as one more (k + l).  The host waits for an update only where
+// it may end the solve of a right-hand side; the flags of the others come back
+// with the next iterations (one that converged all the same sits those out).
 wd_status solver_complete(wd_solver* h) {
   hipError_t e = hipStreamSynchronize(h->s);
   if (e != hipSuccess) return hip_fail(e, "solver iteration");
-  for (int k = 0; k < h->nrhs; ++k)
-    if (!h->done_rhs[k] && h->h_fl[k * FL_COUNT + FL_BREAK]) {
-      e = read_flags(h);  // the breakdown note quotes the scalars
-      if (e != hipSuccess) return hip_fail(e, "solver iteration");
-      break;
-    }
-  {
-    h->loops += h->per_check;
-    bool any_ru = false;
+  e = account(h);
+  if (e != hipSuccess) return hip_fail(e, "solver iteration");
+  h->loops += h->per_check;
+  bool any_ru = false, may_end = false;
+  for (int k = 0; k < h->nrhs; ++k) {
+    if (h->done_rhs[k] || !h->h_fl[k * FL_COUNT + FL_RU]) continue;
+    any_ru = true;
+    may_end |= h->h_fl[k * FL_COUNT + FL_RU] == 2;
+  }
+  if (any_ru) {
+    e = reliable_update(h);
+    // CG: p = r^ + beta p for the updated RHS that iterate on (rumask)
+    if (e == hipSuccess && h->kind == WD_SOLVER_CG)
+      e = blas_cg_p(h->geom, h->prm.inner, h->p, h->rh, h->sc, h->rumask, h->s);
+    if (e != hipSuccess) return hip_fail(e, "reliable update");
+    ++h->loops;
     for (int k = 0; k < h->nrhs; ++k) {
-      if (h->done_rhs[k]) continue;
+      if (h->done_rhs[k] || !h->h_fl[k * FL_COUNT + FL_RU]) continue;
+      ++h->rus[k];
       h->iters[k] = h->h_fl[k * FL_COUNT + FL_ITERS] + h->rus[k];
-      if (h->h_fl[k * FL_COUNT + FL_BREAK]) {
-        h->done_rhs[k] = 1;
-        h->status[k] = WD_EBREAKDOWN;
-        note_breakdown(h, k);
-        continue;
-      }
-      if (h->h_fl[k * FL_COUNT + FL_RU]) any_ru = true;
     }
-    if (any_ru) {
-      e = reliable_update(h);
-      if (e == hipSuccess) e = read_flags(h);
+    if (may_end) {
+      e = read_flags(h, false);
+      if (e == hipSuccess) e = account(h);
       if (e != hipSuccess) return hip_fail(e, "reliable update");
-      ++h->loops;
-      for (int k = 0; k < h->nrhs; ++k) {
-        if (h->done_rhs[k] || !h->h_fl[k * FL_COUNT + FL_RU]) continue;
-        ++h->rus[k];
-        h->iters[k] = h->h_fl[k * FL_COUNT + FL_ITERS] + h->rus[k];
-        if (h->h_fl[k * FL_COUNT + FL_CONV]) {
-          h->done_rhs[k] = 1;
-          h->status[k] = WD_OK;
-        } else if (h->h_fl[k * FL_COUNT + FL_BREAK]) {
-          h->done_rhs[k] = 1;
-          h->status[k] = WD_EBREAKDOWN;
-          note_breakdown(h, k);
-        }
-      }
-      if (h->kind == WD_SOLVER_CG) {
-        // p = r^ + beta p for the updated RHS that iterate on (rumask)
-        e = blas_cg_p(h->geom, h->prm.inner, h->p, h->rh, h->sc, h->rumask, h->s);
-        if (e != hipSuccess) return hip_fail(e, "cg p update");
-      }
     }
   }
   solver_finished(h);
@@ -717,6 +731,7 @@ wd_status wd_solver_end(wd_solver* h, wd_solve_info* info) {
   if (!h) return fail(WD_EINVAL, "solver handle is NULL");
   hipError_t e = reconstruct(h);
   if (e == hipSuccess) e = read_flags(h);
+  if (e == hipSuccess) e = account(h);  // an update that was not waited for
   const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - h->t0).count();
   wd_status result = WD_OK;
   if (e != hipSuccess) result = hip_fail(e, "solver end");
@@ -741,7 +756,6 @@ wd_status wd_solver_end(wd_solver* h, wd_solve_info* info) {
     (void)hipGraphExecDestroy(h->gexec);
     (void)hipGraphDestroy(h->graph);
   }
-  (void)hipHostFree(h->h_fl);
   (void)hipHostFree(h->h_sc);
   const std::string note = h->note;
   delete h;
