@@ -131,10 +131,25 @@ __device__ __forceinline__ void hop_product(const DslashGeom& g, const char* __r
   }
 }
 
+// What a hop left in LDS for this lane's site.
+template <typename R>
+struct HopVals {
+  R w[12], sc;
+};
+template <typename R>
+__device__ __forceinline__ HopVals<R> hop_vals(const R (&wbuf)[8][12][kSplitSites], const R (&sbuf)[8][kSplitSites],
+                                               int slot, int lane) {
+  HopVals<R> q;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) q.w[k] = wbuf[slot][k][lane];
+  q.sc = sbuf[slot][lane];
+  return q;
+}
+
 // acc += scale * (1 -+ gamma) expansion of w, one fused multiply-add per real
 // (mul_acc / mul_acc_half of the one-thread kernels).
 template <int MU, bool BACK, bool DAGGER, int BASIS, typename R>
-__device__ __forceinline__ void hop_accumulate(Spinor<R>& acc, const R* __restrict__ w, R scale) {
+__device__ __forceinline__ void hop_accumulate(Spinor<R>& acc, const HopVals<R>& q) {
   using G = GammaB<MU, BASIS>;
   constexpr int sh = (BACK == DAGGER) ? 2 : 0;
   constexpr int BASE = (BACK == DAGGER) ? 2 : 0;
@@ -142,7 +157,8 @@ __device__ __forceinline__ void hop_accumulate(Spinor<R>& acc, const R* __restri
   for (int k = 0; k < 2; ++k)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const cx<R> z = {w[(6 * k + 2 * a) * kSplitSites], w[(6 * k + 2 * a + 1) * kSplitSites]};
+      const cx<R> z = {q.w[6 * k + 2 * a], q.w[6 * k + 2 * a + 1]};
+      const R scale = q.sc;
       if constexpr (MU == 3 && BASIS == kBasisUK) {
         cx<R>& t = acc.v[BASE + k][a];
         t = {fmar(scale, z.re, t.re), fmar(scale, z.im, t.im)};
@@ -315,15 +331,21 @@ __global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW>())) dslash_spl
   }
   __syncthreads();
   if (hop != 0) return;
-  // a fence after each hop keeps its 12 LDS reads from piling up in registers
+  // a fence after each hop keeps the LDS reads of all of them from piling up in
+  // registers; without a dot (AHEAD) there is room for the next hop's reads
+  // beside this one's arithmetic
+  constexpr bool AHEAD = DOT == DOT_NONE && !XPAY && S::prec != WD_FP64;
   Spinor<R> acc[1];
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int c = 0; c < 3; ++c) acc[0].v[s][c] = {R(0), R(0)};
-#define WD_ACC(MU, BACK, SLOT)                                                                       \
-  hop_accumulate<MU, BACK, DAGGER, BASIS>(acc[0], &wbuf[SLOT][0][lane], sbuf[SLOT][lane]);           \
-  hop_fence<R, 1>(acc)
+  HopVals<R> q = hop_vals<R>(wbuf, sbuf, 0, lane), qn;
+#define WD_ACC(MU, BACK, SLOT)                                                      \
+  if constexpr (AHEAD && SLOT < 7) qn = hop_vals<R>(wbuf, sbuf, SLOT + 1, lane);    \
+  hop_accumulate<MU, BACK, DAGGER, BASIS>(acc[0], q);                               \
+  hop_fence<R, 1>(acc);                                                             \
+  if constexpr (SLOT < 7) q = AHEAD ? qn : hop_vals<R>(wbuf, sbuf, SLOT + 1, lane)
   WD_ACC(0, false, 0);
   WD_ACC(0, true, 1);
   WD_ACC(1, false, 2);
