@@ -1139,8 +1139,13 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         for (int c = 0; c < 3; ++c) acc.v[s][c] = b.v[s][c] - acc.v[s][c];
     }
     if constexpr (DOT != DOT_RES_ENC && DOT != DOT_ENC) {
-      if (g.out_nt) store_spinor<S, true>(out, r, cb, acc);
-      else store_spinor<S>(out, r, cb, acc);
+      if (g.out_nt) {
+        asm volatile("; streaming stores");  // else the compiler merges the two branches into plain stores
+        store_spinor<S, true>(out, r, cb, acc);
+        asm volatile("; end of streaming stores");
+      } else {
+        store_spinor<S>(out, r, cb, acc);
+      }
     }
   }
   if constexpr (DOT == DOT_ENC) {

@@ -11,8 +11,10 @@
 // Launches with a fused dot product keep one sub-slab and 256-thread
 // workgroups, so each partial record covers a fixed set of sites and the
 // reductions give the same bits for every tuned shape; their search covers
-// nr, lds, rloop and wgs.  (link_nt, a cache hint for link loads, and out_nt
-// are still parsed but not searched: neither paid on the lattices measured.)
+// nr, lds, rloop and wgs.  Large launches search with streaming output stores
+// (out_nt, see streams_output) and try the caps without them as well.
+// (link_nt, a cache hint for link loads, is still parsed but not searched: it
+// did not pay on the lattices measured.)
 //
 // A key is (lattice, precision, RHS count of the launch, link format and
 // basis, form), the form being adjoint or not, xpay or not, the fused dot,
@@ -34,7 +36,7 @@
 //
 // WD_TUNE=0 disables tuning; WD_TUNE_CACHE=<file> keeps the choices across
 // processes (one "Lx Ly Lz Lt prec nrhs flags form nr block gslow nsub
-// link_nt lds rloop wgs" line per entry; flags = 1 for 8-real links + 2 for
+// nt lds rloop wgs" line per entry, nt = link_nt + 2 * out_nt; flags = 1 for 8-real links + 2 for
 // temporal gauge + 4 for UKQCD-basis fields; form = 1 adjoint + 2 xpay +
 // 4 * dot mode + 32 mapped subset); WD_TUNE_VERBOSE=1 prints every timed
 // candidate to stderr (the final re-timings marked "re-timed");
@@ -78,6 +80,48 @@ Key key_of(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
              (g->recon == 8 ? 1 : 0) | (g->tgauge ? 2 : 0) | (d.basis == kBasisUK ? 4 : 0), form_of(d)};
 }
 
+// Bytes of a launch: its links once, every right-hand side's input and output.
+int64_t launch_bytes(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
+  const int64_t site = is_half(prec) ? 52 : (prec == WD_FP64 ? 192 : 96);
+  return (int64_t)g->geom.Vh * (8 * link_bytes(prec, g->recon) + 2 * launch_rhs(d) * site);
+}
+
+// Whether a launch's output stores are marked streaming (evicted first), so
+// that neighbours and links keep the caches.  It pays once the launch is well
+// past the 256 MB last-level cache; below, the next launch would have found the
+// output there.  Measured, plain / streaming in microseconds: one right-hand
+// side FP64 48^3x96 1286 / 1228, FP32 32^3x96 (906 MB) 182 / 176, binary16
+// 48^3x64 (1.05 GB) 226 / 211, 40^3x64 (606 MB) 126 / 129, FP32 32^3x64 (604 MB)
+// 122 / 126; twelve binary16 24^3x32 (318 MB) 119 / 104, FP64 32^3x64 2044 /
+// 1938, FP32 48^3x96 4855 / 4607; three binary16 24^3x32 (111 MB) 33 / 35.
+bool streams_output(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
+  const int64_t mb = launch_bytes(g, prec, d) >> 20;
+  return launch_rhs(d) == 1 ? mb >= 800 : mb >= 290;
+}
+
+// Where one wavefront per hop (wd_dslash_split.h) replaces the searched
+// shapes: by the bytes of the launch (links once, every right-hand side's
+// input and output), so that the choice needs no timing.  It wins while the
+// launch stays in the 256 MB last-level cache, where the one-thread kernels
+// wait on latency with the bandwidth unused, and loses once HBM sets the
+// pace.  Measured, best one-thread shape against it in microseconds: FP64
+// 24^3x32 (255 MB) 61 / 45, 24^3x48 (382 MB) 84 / 88, 16^3x32 with 12
+// right-hand sides (352 MB) 121 / 157; FP32 32^3x32 (302 MB) 60 / 55, 32^3x64
+// (604 MB) 120 / 129; one 16-bit right-hand side 32^3x32 (155 MB) 36 / 29,
+// 32^3x64 (310 MB) 64 / 71.  Several 16-bit right-hand sides share their links
+// in the one-thread kernels, and the rebuilt third row is a large part of
+// their work: level from about 131,072 site right-hand sides (16^3x32 with 2:
+// 10.4 / 10.3, 20x14x10x18 with 5: 10.2 / 10.6, with 12: 17.0 / 18.5).
+bool split_pays(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
+  const int64_t Vh = g->geom.Vh, n = launch_rhs(d), bytes = launch_bytes(g, prec, d);
+  if (is_half(prec)) return n == 1 ? bytes <= (200 << 20) : Vh * n <= (1 << 17);
+  // the residual forms end in long FP64 epilogues, which the split kernel's one
+  // finishing wavefront takes alone: 8^4 11.0 / 7.1, 24^3x32 64.8 / 74.3
+  const bool residual = d.xpay && (d.dot == DOT_RES || d.dot == DOT_RES_ENC || d.dot == DOT_ENC);
+  if (residual && Vh * n > (1 << 16)) return false;
+  return bytes <= (prec == WD_FP64 ? (256 << 20) : (300 << 20));
+}
+
 LaunchCfg default_cfg(int nrhs) { return LaunchCfg{nrhs == 1 ? 1 : 2, 256}; }
 
 // A configuration the launchers accept: 128 or 256 threads (512 for the RHS
@@ -105,7 +149,8 @@ void load_cache_locked() {
   int v[16];
   while (std::fscanf(f, "%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d", &v[0], &v[1], &v[2], &v[3], &v[4], &v[5],
                      &v[6], &v[7], &v[8], &v[9], &v[10], &v[11], &v[12], &v[13], &v[14], &v[15]) == 16) {
-    LaunchCfg c{v[8], v[9], v[10], v[11], v[12]};
+    LaunchCfg c{v[8], v[9], v[10], v[11], v[12] & 1};
+    c.out_nt = v[12] >> 1;
     c.lds = v[13];
     c.rloop = v[14];
     c.wgs = v[15];
@@ -121,7 +166,8 @@ void save_entry_locked(const Key& k, const LaunchCfg& c) {
   if (!f) return;
   std::fprintf(f, "%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", std::get<0>(k), std::get<1>(k),
                std::get<2>(k), std::get<3>(k) / 8, std::get<3>(k) % 8, std::get<4>(k), std::get<5>(k),
-               std::get<6>(k), c.nr, c.block, c.gslow, c.nsub, c.link_nt, c.lds, c.rloop, c.wgs);
+               std::get<6>(k), c.nr, c.block, c.gslow, c.nsub, c.link_nt + 2 * c.out_nt, c.lds, c.rloop,
+               c.wgs);
   std::fclose(f);
 }
 
@@ -172,6 +218,7 @@ struct Search {
   LaunchCfg best;
   float best_ms = -1.0f;
   std::vector<std::pair<LaunchCfg, float>> tried;  // every shape that launched, with its time
+  int out_nt = 0;  // of every candidate: by rule, not searched
 
   void report(const LaunchCfg& c, const char* tag, float ms) const {
     if (verbose())
@@ -183,7 +230,8 @@ struct Search {
   }
 
   // the better of two timings, so that a clock ramp-up does not decide
-  void try_cfg(const LaunchCfg& c) {
+  void try_cfg(LaunchCfg c) {
+    c.out_nt = out_nt;
     float ms = time_cfg(g, prec, d, c, s);
     const float ms2 = time_cfg(g, prec, d, c, s);
     if (ms2 > 0.0f && (ms < 0.0f || ms2 < ms)) ms = ms2;
@@ -232,6 +280,7 @@ LaunchCfg run_tuner(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStr
   const bool slab = g->geom.L[2] % 8 == 0;
   const int max_nsub = (dot || mapped) ? 1 : (slab ? 4 : 1);
   Search S{g, prec, d, s, default_cfg(n)};
+  S.out_nt = streams_output(g, prec, d);
   // 1. slots, sub-slabs, LDS staging.  One RHS also tries a two-slot thread:
   // its empty slot costs arithmetic but no memory traffic, and in FP64 the
   // two-slot kernel has measured faster.
@@ -271,12 +320,16 @@ LaunchCfg run_tuner(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStr
       S.try_cfg(c);
     }
   }
-  // 3. occupancy cap of the winner: at most wgs workgroups per CU
-  {
+  // 3. occupancy cap of the winner: at most wgs workgroups per CU; with
+  //    streaming stores also each cap (and none) without them
+  for (int nt = S.out_nt; nt >= 0; --nt) {
     const LaunchCfg w = S.best;
     const int per_wg = w.block / 64;  // waves per workgroup
-    for (int wgs : {2, 3, 4, 6}) {
-      if (wgs * per_wg > 32) continue;  // no tighter than the 8 waves per SIMD a CU holds
+    const bool plain = nt < streams_output(g, prec, d);
+    S.out_nt = nt;
+    for (int wgs : {0, 2, 3, 4, 6}) {
+      if (wgs == 0 && !plain) continue;  // timed already
+      if (wgs * per_wg > 32) continue;   // no tighter than the 8 waves per SIMD a CU holds
       LaunchCfg c = w;
       c.wgs = wgs;
       S.try_cfg(c);
@@ -288,31 +341,6 @@ LaunchCfg run_tuner(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStr
 }
 
 }  // namespace
-
-// Where one wavefront per hop (wd_dslash_split.h) replaces the searched
-// shapes: by the bytes of the launch (links once, every right-hand side's
-// input and output), so that the choice needs no timing.  It wins while the
-// launch stays in the 256 MB last-level cache, where the one-thread kernels
-// wait on latency with the bandwidth unused, and loses once HBM sets the
-// pace.  Measured, best one-thread shape against it in microseconds: FP64
-// 24^3x32 (255 MB) 61 / 45, 24^3x48 (382 MB) 84 / 88, 16^3x32 with 12
-// right-hand sides (352 MB) 121 / 157; FP32 32^3x32 (302 MB) 60 / 55, 32^3x64
-// (604 MB) 120 / 129; one 16-bit right-hand side 32^3x32 (155 MB) 36 / 29,
-// 32^3x64 (310 MB) 64 / 71.  Several 16-bit right-hand sides share their links
-// in the one-thread kernels, and the rebuilt third row is a large part of
-// their work: level from about 131,072 site right-hand sides (16^3x32 with 2:
-// 10.4 / 10.3, 20x14x10x18 with 5: 10.2 / 10.6, with 12: 17.0 / 18.5).
-static bool split_pays(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
-  const int64_t Vh = g->geom.Vh, n = launch_rhs(d);
-  const int64_t site = is_half(prec) ? 52 : (prec == WD_FP64 ? 192 : 96);
-  const int64_t bytes = Vh * (8 * link_bytes(prec, g->recon) + 2 * n * site);
-  if (is_half(prec)) return n == 1 ? bytes <= (200 << 20) : Vh * n <= (1 << 17);
-  // the residual forms end in long FP64 epilogues, which the split kernel's one
-  // finishing wavefront takes alone: 8^4 11.0 / 7.1, 24^3x32 64.8 / 74.3
-  const bool residual = d.xpay && (d.dot == DOT_RES || d.dot == DOT_RES_ENC || d.dot == DOT_ENC);
-  if (residual && Vh * n > (1 << 16)) return false;
-  return bytes <= (prec == WD_FP64 ? (256 << 20) : (300 << 20));
-}
 
 static LaunchCfg searched_config(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStream_t s);
 
@@ -339,12 +367,14 @@ static LaunchCfg searched_config(const wd_gauge* g, wd_prec prec, const DslashAr
     auto it = g_cache.find(k);
     if (it != g_cache.end()) return it->second;
   }
-  if (!tuning_enabled() || d.no_tune) return default_cfg(nrhs);
+  LaunchCfg plain = default_cfg(nrhs);
+  plain.out_nt = streams_output(g, prec, d);
+  if (!tuning_enabled() || d.no_tune) return plain;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return default_cfg(nrhs);
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return plain;
   // repeated launches must leave the result unchanged: no output may alias an input
   if ((d.xpay && d.xpay->ptr == d.out.ptr) || (d.y && d.y->ptr == d.out.ptr) || d.in.ptr == d.out.ptr)
-    return default_cfg(nrhs);
+    return plain;
   const LaunchCfg best = run_tuner(g, prec, d, s);
   std::lock_guard<std::mutex> lock(g_mu);
   g_cache[k] = best;
