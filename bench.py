@@ -99,11 +99,11 @@ def dslash_bytes_links(prec: str, nrhs: int, recon: int, temporal: bool, lt: int
 
 def bicgstab_iter_bytes(prec: str, nrhs: int) -> int:
     """One BiCGstab iteration for nrhs RHS, per site: 2 M_hat (4 dslash, the
-    second of each with the xpay read and, for v, the <r~,v> read of r~) and
-    the BLAS-1 passes (p: 3R+1W, s: 2R+1W, x/r: 5R+2W)."""
+    second of each with the xpay read and the read of r~ for its dots) and
+    the BLAS-1 passes (s: 2R+1W, x/r/p: 5R+3W)."""
     s = SPINOR_B[prec]
-    return (dslash_bytes(prec, nrhs) * 2 + dslash_bytes(prec, nrhs, 1) * 2 + nrhs * s  # <r~,v>
-            + nrhs * s * (4 + 3 + 7))
+    return (dslash_bytes(prec, nrhs) * 2 + dslash_bytes(prec, nrhs, 2) * 2  # + r~
+            + nrhs * s * (3 + 8))
 
 
 def ru_bytes(prec: str, nrhs: int) -> int:
@@ -431,7 +431,7 @@ def profile_summary(args) -> None:
     # xpay source and y where the form reads them
     def alg_reads(d):
         n = d["nrhs"] or NRHS
-        per = SPINOR_B[d["prec"]] * (1 + d["xpay"] + (d["dot"] in (1, 4, 5)))
+        per = SPINOR_B[d["prec"]] * (1 + d["xpay"] + (d["dot"] in (1, 2, 4, 5)))
         return Vh * (8 * LINK_B[d["prec"]] + n * per)
 
     def label(d):

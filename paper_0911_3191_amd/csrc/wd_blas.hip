@@ -58,13 +58,18 @@ __device__ __forceinline__ void load_part(const FieldView& f, int r, int64_t i, 
   }
 }
 template <class S, bool SPLIT>
-__device__ __forceinline__ void store_part(const FieldView& f, int r, int64_t i, const Part<S, SPLIT>& q) {
+__device__ __forceinline__ void store_part(const FieldView& f, int r, int64_t i, const Part<S, SPLIT>& q,
+                                           Part<S, SPLIT>* back = nullptr) {
   if constexpr (!SPLIT) {
-    Spinor<typename S::real> a;
+    Spinor<typename S::real> a, e;
 #pragma unroll
     for (int n = 0; n < 12; ++n) a.v[n / 3][n % 3] = q.v[n];
-    store_spinor<S>(f, r, i, a);
+    store_spinor<S>(f, r, i, a, back ? &e : nullptr);
+    if (back)
+#pragma unroll
+      for (int n = 0; n < 12; ++n) back->v[n] = e.v[n / 3][n % 3];
   } else {
+    if (back) *back = q;
     constexpr int PER = Part<S, SPLIT>::N / 3;
     const int k0 = 3 * (threadIdx.x / Part<S, SPLIT>::kSites);
 #pragma unroll
@@ -120,47 +125,43 @@ __global__ void __launch_bounds__(kBlock) k_bicg_s(int Vh, FieldView r, FieldVie
 }
 
 // x <- x + alpha p + omega s;  r <- s - omega t  (s lives in r);
-// partials: |r|^2, <r~, r>
+// p <- r + beta (p - omega v), unless the right-hand side pauses for a
+// reliable update, which re-seeds r first.  Eight fields moved; as an x/r update
+// with <r~, r> and |r|^2 and a p update it was eleven (and two launches more),
+// see FIN_BICG_OMEGA.  32^3x64, binary16, 12 RHS: 931 us (5.8 TB/s) instead of
+// 888 + 488; the launch that now also reads r~ takes 721 instead of 604.
 template <class S, bool SPLIT>
-__global__ void __launch_bounds__(kBlock) k_bicg_xr(int Vh, FieldView x, FieldView r, FieldView p,
-                                                    FieldView t, FieldView rt,
-                                                    const double* __restrict__ sc,
-                                                    const int* __restrict__ mask,
-                                                    double* __restrict__ partials, FinArgs fa) {
+__global__ void __launch_bounds__(kBlock) k_bicg_xrp(int Vh, FieldView x, FieldView r, FieldView p, FieldView t,
+                                                     FieldView v, const double* __restrict__ sc,
+                                                     const int* __restrict__ fl, int step) {
   using R = typename S::real;
   const int rhs = blockIdx.y;
-  if (mask && !mask[rhs]) return;
+  const int ru = fl[rhs * FL_COUNT + FL_RU];
+  if (ru >> 2 != step + 1) return;
+  const bool go_on = (ru & 3) == 0;
   const int i = part_site<S, SPLIT>();
-  double d[3] = {0.0, 0.0, 0.0};
-  if (i < Vh) {
-    const double* s = sc + rhs * SC_COUNT;
-    const cx<R> al = cload<R>(s, SC_ALPHA), om = cload<R>(s, SC_OMEGA);
-    Part<S, SPLIT> X, Ss, P, T, Rt;
-    load_part<S, SPLIT>(x, rhs, i, X);
-    load_part<S, SPLIT>(r, rhs, i, Ss);
-    load_part<S, SPLIT>(p, rhs, i, P);
-    load_part<S, SPLIT>(t, rhs, i, T);
-    load_part<S, SPLIT>(rt, rhs, i, Rt);
-    R nn = 0, re = 0, im = 0;
+  if (i >= Vh) return;
+  const double* s = sc + rhs * SC_COUNT;
+  const cx<R> al = cload<R>(s, SC_ALPHA), om = cload<R>(s, SC_OMEGA);
+  const cx<R> b = {static_cast<R>(s[SC_BETA]), static_cast<R>(s[SC_BETA_IM])};
+  Part<S, SPLIT> X, Ss, P, T, Vv;
+  load_part<S, SPLIT>(x, rhs, i, X);
+  load_part<S, SPLIT>(r, rhs, i, Ss);
+  load_part<S, SPLIT>(p, rhs, i, P);
+  load_part<S, SPLIT>(t, rhs, i, T);
+  if (go_on) load_part<S, SPLIT>(v, rhs, i, Vv);
 #pragma unroll
-    for (int n = 0; n < Part<S, SPLIT>::N; ++n) {
-      X.v[n] = X.v[n] + al * P.v[n] + om * Ss.v[n];
-      const cx<R> rn = Ss.v[n] - om * T.v[n];
-      Ss.v[n] = rn;
-      nn += rn.re * rn.re + rn.im * rn.im;
-      const cx<R> q = cmulc(Rt.v[n], rn);
-      re += q.re;
-      im += q.im;
-    }
-    store_part<S, SPLIT>(x, rhs, i, X);
-    store_part<S, SPLIT>(r, rhs, i, Ss);
-    d[0] = nn;
-    d[1] = re;
-    d[2] = im;
+  for (int n = 0; n < Part<S, SPLIT>::N; ++n) {
+    X.v[n] = X.v[n] + al * P.v[n] + om * Ss.v[n];
+    Ss.v[n] = Ss.v[n] - om * T.v[n];
   }
-  double* rec = partials + (int64_t)rhs * gridDim.x * kMaxDot;
-  if (fa.stage < 0) block_sum_store<3>(d, rec + blockIdx.x * kMaxDot);
-  else block_sum_finalize<3>(d, rec, blockIdx.x, gridDim.x, rhs, fa);
+  store_part<S, SPLIT>(x, rhs, i, X);
+  Part<S, SPLIT> Rr;  // p follows the stored r
+  store_part<S, SPLIT>(r, rhs, i, Ss, &Rr);
+  if (!go_on) return;
+#pragma unroll
+  for (int n = 0; n < Part<S, SPLIT>::N; ++n) P.v[n] = Rr.v[n] + b * (P.v[n] - om * Vv.v[n]);
+  store_part<S, SPLIT>(p, rhs, i, P);
 }
 
 // ---- CG on the normal equations ---------------------------------------------------
@@ -373,6 +374,7 @@ __global__ void __launch_bounds__(kBlock) k_reencode(int Vh, FieldView rh, Field
 // one workgroup, with its scalars in flight meanwhile.  512 threads, wavefront
 // shuffles and one barrier: 8^4 3.0 -> 2.7 us, 24^3x32 with wave records
 // 5.3 -> 5.2 us on average (it waits for other XCDs' records).
+template <int N>
 __global__ void __launch_bounds__(kFinBlock) k_finalize(int nb, int waves, const double* __restrict__ partials,
                                                         const int* __restrict__ mask, FinArgs fa) {
   const int rhs = blockIdx.x;
@@ -380,10 +382,13 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(int nb, int waves, const
   const double* s = fa.sc + rhs * SC_COUNT;
   __shared__ double q[SC_COUNT];  // the scalars as they were
   const double own = threadIdx.x < SC_COUNT ? s[threadIdx.x] : 0.0;
-  double v[4];  // component 3: FIN_TRUE_RHO only (other stages leave it unset)
-  sum_partials(partials + (int64_t)rhs * nb * (waves ? 4 : 1) * kMaxDot, nb, waves != 0, v,
-               [&] { if (threadIdx.x < SC_COUNT) q[threadIdx.x] = own; });
-  if (threadIdx.x == 0) apply_stage(fa, rhs, v, q);
+  double r[N], v[kWideDot] = {};  // a stage reads the components that its records have
+  sum_partials<N>(partials + (int64_t)rhs * nb * (waves ? 4 : 1) * N, nb, waves != 0, r,
+                  [&] { if (threadIdx.x < SC_COUNT) q[threadIdx.x] = own; });
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = r[k];
+  apply_stage(fa, rhs, v, q);
 }
 
 // CG stopping: at a reliable update the true residual |r| of M_hat x = b_hat is
@@ -462,13 +467,13 @@ hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double
   });
 }
 
-hipError_t blas_bicg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field rt,
-                        const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s) {
+hipError_t blas_bicg_xrp(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field v, const double* sc,
+                         const int* fl, int step, hipStream_t s) {
   return by_prec(pr, [&](auto tag) {
     using S = decltype(tag);
     by_split<S>(g, x.nrhs, [&](dim3 grid, auto split) {
-      k_bicg_xr<S, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(t), fv(rt), sc,
-                                                                   mask, partials, fa);
+      k_bicg_xrp<S, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(t), fv(v), sc, fl,
+                                                                    step);
     });
   });
 }
@@ -545,7 +550,8 @@ hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r6
 
 hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, const int* mask,
                            hipStream_t s) {
-  k_finalize<<<nrhs, kFinBlock, 0, s>>>(nb, waves, partials, mask, fa);
+  if (fa.stage == FIN_BICG_OMEGA) k_finalize<kWideDot><<<nrhs, kFinBlock, 0, s>>>(nb, waves, partials, mask, fa);
+  else k_finalize<kMaxDot><<<nrhs, kFinBlock, 0, s>>>(nb, waves, partials, mask, fa);
   return hipGetLastError();
 }
 

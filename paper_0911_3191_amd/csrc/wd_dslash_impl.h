@@ -1056,7 +1056,8 @@ __device__ __forceinline__ void hop_pair(Spinor<typename S::real> (&acc)[NR], co
 // out = D in, or out = x + a * D in (XPAY), optionally followed by per-block
 // FP64 partial dot products of the result (DOT):
 //   DOT_YO: <y, out>                 (complex; BiCGstab <r~, v>)
-//   DOT_OX: <out, x>, |out|^2        (BiCGstab <t, s>, <t, t> with x = s)
+//   DOT_OX: <out, x>, |out|^2, <y, out>, <y, x>, |x|^2 of the stored out
+//                                    (BiCGstab: t = out, s = x, r~ = y)
 //   DOT_OO: |out|^2                  (CG |M p|^2)
 //   DOT_RES: out = y - (x + a * D in), |out|^2 (FP64 residual b_hat - M_hat x)
 //   DOT_RES_ENC: r = y - (x + a * D in) re-encoded in format S2 into enc.rh
@@ -1105,9 +1106,9 @@ template <int N, bool WAVE>
 __device__ __forceinline__ void sum_store(double (&d)[N], double* rec, int pid, int nb, int r, const FinArgs& fa) {
   if constexpr (WAVE) {
     if (fa.stage >= 0) wave_sum_finalize<N>(d, rec, pid, nb, r, fa);
-    else wave_sum_store<N>(d, rec + (int64_t)pid * kMaxDot);
+    else wave_sum_store<N>(d, rec + (int64_t)pid * kRecord<N>);
   } else {
-    block_sum_store<N>(d, rec + (int64_t)pid * kMaxDot);
+    block_sum_store<N>(d, rec + (int64_t)pid * kRecord<N>);
   }
 }
 
@@ -1138,7 +1139,17 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
 #pragma unroll
         for (int c = 0; c < 3; ++c) acc.v[s][c] = b.v[s][c] - acc.v[s][c];
     }
-    if constexpr (DOT != DOT_RES_ENC && DOT != DOT_ENC) {
+    if constexpr (DOT == DOT_OX) {
+      Spinor<R> back;  // the dots see the stored value
+      if (g.out_nt) {
+        asm volatile("; streaming stores");
+        store_spinor<S, true>(out, r, cb, acc, &back);
+        asm volatile("; end of streaming stores");
+      } else {
+        store_spinor<S>(out, r, cb, acc, &back);
+      }
+      acc = back;
+    } else if constexpr (DOT != DOT_RES_ENC && DOT != DOT_ENC) {
       if (g.out_nt) {
         asm volatile("; streaming stores");  // else the compiler merges the two branches into plain stores
         store_spinor<S, true>(out, r, cb, acc);
@@ -1231,21 +1242,32 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
       }
       sum_store<2, WAVE>(d, part, pid, nb, r, enc.fin);
     } else if constexpr (DOT == DOT_OX) {
-      double d[3] = {0.0, 0.0, 0.0};
+      double d[kWideDot] = {};
       if (valid) {
-        R re = 0, im = 0, nn = 0;
+        Spinor<R> y;
+        if constexpr (WAVE) y = *yw;
+        else load_spinor<S>(ys, r, cb, y);
+        R re = 0, im = 0, nn = 0, yre = 0, yim = 0, xre = 0, xim = 0, xx = 0;
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             acc_cdotc(re, im, acc.v[s][c], x.v[s][c]);
             acc_norm(nn, acc.v[s][c]);
+            acc_cdotc(yre, yim, y.v[s][c], acc.v[s][c]);
+            acc_cdotc(xre, xim, y.v[s][c], x.v[s][c]);
+            acc_norm(xx, x.v[s][c]);
           }
         d[0] = re;
         d[1] = im;
         d[2] = nn;
+        d[3] = yre;
+        d[4] = yim;
+        d[5] = xre;
+        d[6] = xim;
+        d[7] = xx;
       }
-      sum_store<3, WAVE>(d, part, pid, nb, r, enc.fin);
+      sum_store<8, WAVE>(d, partials + (int64_t)r * nb * kWideDot, pid, nb, r, enc.fin);
     } else {
       double d[1] = {0.0};
       if (valid) {

@@ -204,7 +204,7 @@ constexpr int kTileRow = 13;    // 16-byte slots per record: 12 and one of paddi
 // Moves the records of n consecutive lanes' sites between the canonical array
 // and the tile; rec: this lane's record number (CONTIG: those of the lanes
 // follow one another).  The library never reads back what it writes here, so
-// the stores are marked streaming (24^3x32 binary16 decode 11.2 -> 8.3 us).
+// the stores are marked streaming (24^3x32 binary16 decode 11.2 -> 9.5 us).
 template <bool CONTIG, bool STORE>
 __device__ __forceinline__ void move_records(double2* __restrict__ canon, double2* __restrict__ tile, int rec, int n) {
   const int lane = threadIdx.x;

@@ -25,7 +25,7 @@ __device__ __forceinline__ void store_beta(double* s, cx<double> rho, cx<double>
 
 // Stage fa.stage of one right-hand side from its summed records v; q: its
 // scalars as they were.
-__device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const double (&v)[4], const double* q) {
+__device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const double (&v)[kWideDot], const double* q) {
   double* s = fa.sc + rhs * SC_COUNT;
   int* f = fa.fl + rhs * FL_COUNT;
   int* active = fa.active;
@@ -49,7 +49,7 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
       if (!isfinite(v[0])) f[FL_BREAK] = stage + 1;
       // iteration resumes (an RHS that triggered the update was paused) unless done
       active[rhs] = (f[FL_CONV] || f[FL_BREAK]) ? 0 : 1;
-      // FL_RU stays as the iteration set it: the host counts the update from it
+      f[FL_RU] &= 3;  // the trigger stays as the iteration set it: the host counts the update from it
       rumask[rhs] = active[rhs];  // the residual is re-seeded only where iteration goes on
       break;
     }
@@ -66,6 +66,7 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
       s[SC_MMAX] = sqrt(v[0]);
       f[FL_CONV] = (sqrt(v[0]) <= stop) ? 1 : 0;
       if (!isfinite(v[0])) f[FL_BREAK] = FIN_TRUE + 1;
+      f[FL_RU] &= 3;
       active[rhs] = (f[FL_CONV] || f[FL_BREAK]) ? 0 : 1;
       rumask[rhs] = active[rhs];
       if (active[rhs]) {
@@ -95,6 +96,7 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
     }
     case FIN_BICG_ALPHA: {  // alpha = rho / <r~, v>
       ++f[FL_ITERS];
+      f[FL_RU] = 0;
       const cx<double> d = {v[0], v[1]};
       if (!(d.re * d.re + d.im * d.im > 0.0) || !isfinite(d.re) || !isfinite(d.im)) {
         f[FL_BREAK] = stage + 1;
@@ -106,43 +108,50 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
       s[SC_ALPHA + 1] = a.im;
       break;
     }
-    case FIN_BICG_OMEGA: {  // omega = <t, s> / <t, t>
-      if (v[2] == 0.0 && v[0] == 0.0 && v[1] == 0.0) {
+    case FIN_BICG_OMEGA: {
+      // v = <t, s>, |t|^2, <r~, t>, <r~, s>, |s|^2 of the stored t and s:
+      // omega = <t, s> / <t, t>, and for r = s - omega t at once rho = <r~, r>,
+      // beta and |r|^2, so that one update can take x, r and p
+      const cx<double> ts = {v[0], v[1]}, rt = {v[3], v[4]}, rs = {v[5], v[6]};
+      const double t2 = v[2], s2 = v[7];
+      cx<double> om;
+      if (t2 == 0.0 && ts.re == 0.0 && ts.im == 0.0) {
         // t = M_hat s = 0 means s = 0: the step already solved the system and
         // omega is arbitrary; 1 keeps the next beta finite (r becomes 0 and a
         // reliable update follows)
-        s[SC_OMEGA] = 1.0;
-        s[SC_OMEGA + 1] = 0.0;
-        break;
-      }
-      if (!(v[2] > 0.0) || !isfinite(v[2])) {
+        om = one;
+      } else if (!(t2 > 0.0) || !isfinite(t2)) {
         f[FL_BREAK] = stage + 1;
         active[rhs] = 0;
         break;
+      } else {
+        om = {ts.re / t2, ts.im / t2};
       }
-      s[SC_OMEGA] = v[0] / v[2];
-      s[SC_OMEGA + 1] = v[1] / v[2];
-      break;
-    }
-    case FIN_BICG_ITER: {  // |r^|^2, <r~, r^>; reliable-update trigger
+      const cx<double> rho = rs - om * rt;
+      const double r2 = s2 - 2.0 * (om.re * ts.re + om.im * ts.im) + (om.re * om.re + om.im * om.im) * t2;
+      if (!isfinite(r2) || !isfinite(rho.re) || !isfinite(rho.im) ||
+          !(om.re * om.re + om.im * om.im > 0.0)) {
+        f[FL_BREAK] = FIN_BICG_ITER + 1;
+        active[rhs] = 0;
+        break;
+      }
+      s[SC_OMEGA] = om.re;
+      s[SC_OMEGA + 1] = om.im;
       s[SC_RHOP] = rho0.re;
       s[SC_RHOP + 1] = rho0.im;
-      s[SC_RHO] = v[1];
-      s[SC_RHO + 1] = v[2];
-      s[SC_R2] = v[0];
-      store_beta(s, {v[1], v[2]}, rho0, alpha0, omega0);
-      const double rn = sqrt(v[0]);
-      if (!isfinite(rn) || !(omega0.re * omega0.re + omega0.im * omega0.im > 0.0)) {
-        f[FL_BREAK] = stage + 1;
-        active[rhs] = 0;
-        break;
-      }
+      s[SC_RHO] = rho.re;
+      s[SC_RHO + 1] = rho.im;
+      store_beta(s, rho, rho0, alpha0, om);
+      const double rn = sqrt(fmax(r2, 0.0));
+      s[SC_R2] = fmax(r2, 0.0);
       // reliable updates: against the largest |r^| since the last update;
-      // defect correction: against the residual the inner solve started from
+      // defect correction: against the residual the inner solve started from.
+      // A step that removes all but 1e-3 of s leaves |r|^2 to the rounding of
+      // the terms it is the difference of: the update recomputes r
       const double mmax = fa.restart ? q[SC_MMAX] : fmax(q[SC_MMAX], rn);
       s[SC_MMAX] = mmax;
-      const int ru = rn <= stop ? 2 : (rn < fa.delta * mmax ? 1 : 0);
-      f[FL_RU] = ru;
+      const int ru = rn <= stop ? 2 : (rn < fa.delta * mmax || r2 < 1e-6 * s2 ? 1 : 0);
+      f[FL_RU] = ru + 4 * (fa.step + 1);  // the update of x and r still runs (see k_bicg_xrp)
       rumask[rhs] = ru != 0;
       if (ru) active[rhs] = 0;  // paused until the host has run the update
       break;
@@ -245,7 +254,7 @@ __device__ __forceinline__ void block_sum_finalize(double (&d)[N], double* rec, 
     double t[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) t[k] = (sm[0][k] + sm[1][k]) + (sm[2][k] + sm[3][k]);
-    last = count_record<N>(t, rec + index * kMaxDot, rhs, count, fa);
+    last = count_record<N>(t, rec + index * kRecord<N>, rhs, count, fa);
   }
   __syncthreads();
   if (!last) return;
@@ -253,14 +262,14 @@ __device__ __forceinline__ void block_sum_finalize(double (&d)[N], double* rec, 
 #pragma unroll
   for (int k = 0; k < N; ++k) v[k] = 0.0;
 #pragma unroll 4
-  for (int i = threadIdx.x; i < count; i += kBlock) read_record<N>(rec + i * kMaxDot, v);
+  for (int i = threadIdx.x; i < count; i += kBlock) read_record<N>(rec + i * kRecord<N>, v);
   wave_sum<N>(v);
   if (lane == 0)
 #pragma unroll
     for (int k = 0; k < N; ++k) sm[wid][k] = v[k];
   __syncthreads();
   if (threadIdx.x != 0) return;
-  double t[4] = {0.0, 0.0, 0.0, 0.0};
+  double t[kWideDot] = {};
 #pragma unroll
   for (int k = 0; k < N; ++k) t[k] = (sm[0][k] + sm[1][k]) + (sm[2][k] + sm[3][k]);
   double q[SC_COUNT];
@@ -279,20 +288,20 @@ __device__ __forceinline__ void wave_sum_finalize(double (&d)[N], double* rec, i
   const int lane = threadIdx.x & 63;
   wave_sum<N>(d);
   int last = 0;
-  if (lane == 0) last = count_record<N>(d, rec + index * kMaxDot, rhs, count, fa);
+  if (lane == 0) last = count_record<N>(d, rec + index * kRecord<N>, rhs, count, fa);
   if (!__builtin_amdgcn_readfirstlane(last)) return;
   double q4[4][N], g[N];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
 #pragma unroll
     for (int n = 0; n < N; ++n) q4[k][n] = 0.0;
-    if (4 * lane < count) read_record<N>(rec + (4 * lane + k) * kMaxDot, q4[k]);
+    if (4 * lane < count) read_record<N>(rec + (4 * lane + k) * kRecord<N>, q4[k]);
   }
 #pragma unroll
   for (int n = 0; n < N; ++n) g[n] = (q4[0][n] + q4[1][n]) + (q4[2][n] + q4[3][n]);
   wave_sum<N>(g);
   if (lane != 0) return;
-  double t[4] = {0.0, 0.0, 0.0, 0.0};
+  double t[kWideDot] = {};
 #pragma unroll
   for (int n = 0; n < N; ++n) t[n] = g[n];
   double q[SC_COUNT];

@@ -80,7 +80,9 @@ enum ScalarSlot {
 };
 // FL_ITERS counts the inner iterations an RHS has started, on the device, so
 // that several iterations can run between two reads of the flags by the host.
-// FL_RU: 0, 1 (the residual has dropped by delta) or 2 (it may have converged).
+// FL_RU: 0, 1 (the residual has dropped by delta) or 2 (it may have converged);
+// BiCGstab adds 4 * (step + 1) while the update of iteration `step` of its
+// batch is to run.
 enum FlagSlot { FL_RU = 0, FL_BREAK = 1, FL_CONV = 2, FL_ITERS = 3, FL_COUNT = 4 };
 enum FinStage {
   FIN_B2, FIN_TRUE, FIN_RHO, FIN_BICG_INIT, FIN_BICG_ALPHA, FIN_BICG_OMEGA,
@@ -101,13 +103,14 @@ struct FinArgs {
   double tol;    // target relative residual
   int restart;   // 1: defect correction (Algorithm 1), 0: reliable updates (Algorithm 2)
   int counter;   // scalar slot whose bits count the workgroups of a fused finalize
+  int step;      // iteration within its batch
 };
 // Most records per RHS that the last workgroup of their kernel sums itself
 // (the figures are in wd_finalize.h).
 constexpr int kFusedRecords = 128;
 
 // ---- launchers (defined in the .hip files; all asynchronous on `s`) -------------
-constexpr int kMaxDotHost = 4;  // doubles per partial record
+constexpr int kMaxDotHost = 4;  // doubles per partial record (DOT_OX: 8)
 // DOT_RES (FP64 only): out = y - (xpay + a D in), the residual of a reliable
 // update, with |out|^2 partials.  DOT_RES_ENC (FP64, UKQCD basis): the same
 // residual r is not stored in FP64 but re-encoded straight into the inner
@@ -231,11 +234,13 @@ hipError_t blas_bicg_p(const Geom& g, wd_prec pr, Field p, Field r, Field v, con
                        const int* mask, hipStream_t s);
 hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double* sc,
                        const int* mask, hipStream_t s);
-// Partial records per RHS that blas_bicg_xr and blas_cg_xr write (up to four
-// times those of the other kernels).
+// Partial records per RHS that blas_cg_xr writes (up to four times those of
+// the other kernels).
 int blas_dot_records(const Geom& g, wd_prec p);
-hipError_t blas_bicg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field rt,
-                        const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s);
+// The x, r and p updates of iteration `step`, for the RHS whose FL_RU names it
+// (p: those that do not pause for a reliable update).
+hipError_t blas_bicg_xrp(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field v, const double* sc,
+                         const int* fl, int step, hipStream_t s);
 hipError_t blas_cg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field q,
                       const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s);
 hipError_t blas_cg_p(const Geom& g, wd_prec pr, Field p, Field r, const double* sc,
@@ -256,7 +261,7 @@ hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r6
 // fa.stage on the nb records per RHS of a launch (waves: wave records, four to
 // each, see DslashArgs::waves).
 hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, const int* mask,
-                           hipStream_t s);
+                           hipStream_t s);  // FIN_BICG_OMEGA: records of 8 doubles
 hipError_t solver_cg_tighten(int nrhs, double* sc, const int* fl, const int* mask, double tol,
                              hipStream_t s);
 hipError_t solver_init_flags(int nrhs, int* fl, int* active, int* rumask, double* sc, int counter, hipStream_t s);

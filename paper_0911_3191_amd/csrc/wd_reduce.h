@@ -12,7 +12,10 @@ namespace wd {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr int kMaxDot = 4;  // components per partial record
+constexpr int kMaxDot = 4;  // doubles per partial record (DOT_OX: kWideDot)
+constexpr int kWideDot = 8;
+template <int N>
+constexpr int kRecord = N > kMaxDot ? kWideDot : kMaxDot;  // record of N components
 
 // Sum v[0..N) over the block; thread 0 writes out[0..N).  Every thread of
 // the block must call it (inactive sites contribute zeros).  The LDS slots
@@ -58,50 +61,53 @@ __device__ __forceinline__ void wave_sum_store(double (&v)[N], double* out) {
     for (int k = 0; k < N; ++k) out[k] = v[k];
 }
 
-// Fixed-order sum of nb partial records (stride kMaxDot) into res[0..4).
+// Fixed-order sum of nb partial records of N doubles (4 or 8) into res.
 // Called by all kFinBlock threads of one block; the result is valid in thread
 // 0.  waves: each record is four wave records (see wave_sum_store).  `before`
 // runs before the barrier.
 constexpr int kFinBlock = 512;
-template <class F>
-__device__ __forceinline__ void sum_partials(const double* part, int nb, bool waves, double (&res)[4], F&& before) {
+template <int N, class F>
+__device__ __forceinline__ void sum_partials(const double* part, int nb, bool waves, double (&res)[N], F&& before) {
   struct Rec {
-    double2 a, b;
+    double2 a[N / 2];
   };
   const Rec* rec = reinterpret_cast<const Rec*>(part);
-  double2 sa = {0.0, 0.0}, sb = {0.0, 0.0};
+  double v[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = 0.0;
   if (waves) {
 #pragma unroll 2
     for (int i = threadIdx.x; i < nb; i += kFinBlock) {
       const Rec r0 = rec[4 * i], r1 = rec[4 * i + 1], r2 = rec[4 * i + 2], r3 = rec[4 * i + 3];
-      sa.x += (r0.a.x + r1.a.x) + (r2.a.x + r3.a.x);
-      sa.y += (r0.a.y + r1.a.y) + (r2.a.y + r3.a.y);
-      sb.x += (r0.b.x + r1.b.x) + (r2.b.x + r3.b.x);
-      sb.y += (r0.b.y + r1.b.y) + (r2.b.y + r3.b.y);
+#pragma unroll
+      for (int k = 0; k < N / 2; ++k) {
+        v[2 * k] += (r0.a[k].x + r1.a[k].x) + (r2.a[k].x + r3.a[k].x);
+        v[2 * k + 1] += (r0.a[k].y + r1.a[k].y) + (r2.a[k].y + r3.a[k].y);
+      }
     }
   } else {
 #pragma unroll 4
     for (int i = threadIdx.x; i < nb; i += kFinBlock) {
       const Rec r = rec[i];
-      sa.x += r.a.x;
-      sa.y += r.a.y;
-      sb.x += r.b.x;
-      sb.y += r.b.y;
+#pragma unroll
+      for (int k = 0; k < N / 2; ++k) {
+        v[2 * k] += r.a[k].x;
+        v[2 * k + 1] += r.a[k].y;
+      }
     }
   }
-  double v[4] = {sa.x, sa.y, sb.x, sb.y};
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] += __shfl_down(v[k], off, 64);
-  __shared__ double sm[kFinBlock / 64][4];
+    for (int k = 0; k < N; ++k) v[k] += __shfl_down(v[k], off, 64);
+  __shared__ double sm[kFinBlock / 64][N];
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) sm[threadIdx.x >> 6][k] = v[k];
+    for (int k = 0; k < N; ++k) sm[threadIdx.x >> 6][k] = v[k];
   before();
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < N; ++k) {
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < kFinBlock / 64; ++w) t += sm[w][k];

@@ -100,21 +100,22 @@ namespace wd {
 // solver does not use otherwise.
 static int counter_slot(int kind) { return kind == WD_SOLVER_CG ? SC_OMEGA : SC_TOLN; }
 
-static FinArgs fin_args(wd_solver* h, int stage) {
+static FinArgs fin_args(wd_solver* h, int stage, int step = 0) {
   return FinArgs{stage, h->sc, h->fl, h->active, h->rumask, h->prm.delta, h->prm.tol, h->prm.restart,
-                 counter_slot(h->kind)};
+                 counter_slot(h->kind), step};
 }
 
 // Room for the wave records of a fused dot: whichever odd temporary the launch
 // does not use (the FP64 one is free while the inner solver iterates, the
 // inner one during prepare and the reliable updates).  stage: the finalize
 // stage that the caller runs next with fin().
-static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d, int stage) {
+static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d, int stage, int step = 0) {
   const bool hi = d.in.ptr == h->to64.ptr || d.out.ptr == h->to64.ptr || (d.xpay && d.xpay->ptr == h->to64.ptr);
   h->wave_records = reinterpret_cast<double*>(hi ? h->to.ptr : h->to64.ptr);
   d.wave_partials = h->wave_records;
+  if (d.dot == DOT_OX) d.partials = h->wave_records;  // records of 8 doubles
   d.waves = &h->waves;
-  d.fin = fin_args(h, stage);
+  d.fin = fin_args(h, stage, step);
   d.finalized = &h->finalized;
   return launch_dslash_ex(h->g, prec, d, h->s);
 }
@@ -123,7 +124,7 @@ static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d, int stag
 // same set as mask), packed into as few RHS groups as they fill.
 static hipError_t dslash_into(wd_solver* h, wd_prec prec, const Field& out, const Field& in,
                               int parity, int dagger, const Field* xpay, double a, int dot,
-                              const Field* y, const int* mask, int n_map = 0, int stage = -1) {
+                              const Field* y, const int* mask, int n_map = 0, int stage = -1, int step = 0) {
   DslashArgs d;
   d.out = out;
   d.in = in;
@@ -140,19 +141,19 @@ static hipError_t dslash_into(wd_solver* h, wd_prec prec, const Field& out, cons
     d.rhs_map = h->rumap;
     d.n_map = n_map;
   }
-  return launch_dot(h, prec, d, stage);
+  return launch_dot(h, prec, d, stage, step);
 }
 
 // out_e = in_e - kappa^2 D_eo D_oe in_e (dagger: the adjoint), optional fused dot.
 static hipError_t mhat_into(wd_solver* h, wd_prec prec, const Field& out, const Field& in,
                             const Field& tmp_odd, int dagger, int dot, const Field* y,
-                            const int* mask, int n_map = 0, int stage = -1) {
+                            const int* mask, int n_map = 0, int stage = -1, int step = 0) {
   hipError_t e = dslash_into(h, prec, tmp_odd, in, 1, dagger, nullptr, 0.0, DOT_NONE, nullptr, mask, n_map);
   if (e != hipSuccess) return e;
-  return dslash_into(h, prec, out, tmp_odd, 0, dagger, &in, -h->kappa * h->kappa, dot, y, mask, n_map, stage);
+  return dslash_into(h, prec, out, tmp_odd, 0, dagger, &in, -h->kappa * h->kappa, dot, y, mask, n_map, stage, step);
 }
 
-// Records of the iteration's x/r update: more than h->partials has room for
+// Records of CG's x/r update: more than h->partials has room for
 // where it splits sites over threads; the FP64 odd temporary is free then.
 static double* xr_records(wd_solver* h) {
   return blas_dot_records(h->geom, h->prm.inner) <= h->nb ? h->partials : reinterpret_cast<double*>(h->to64.ptr);
@@ -161,27 +162,25 @@ static double* xr_records(wd_solver* h) {
 // Finalize stage on the records of the last launch, unless that launch ran it
 // itself.  after_dslash: they come from a dslash with a fused dot, else from a
 // BLAS-1 kernel.
-static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash) {
+static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash, int step = 0) {
   if (after_dslash) {
     if (h->finalized) return hipSuccess;
-    return solver_finalize(fin_args(h, stage), h->nrhs, h->nb_dslash, h->waves,
-                           h->waves ? h->wave_records : h->partials, mask, h->s);
+    return solver_finalize(fin_args(h, stage, step), h->nrhs, h->nb_dslash, h->waves,
+                           h->waves || stage == FIN_BICG_OMEGA ? h->wave_records : h->partials, mask, h->s);
   }
   return solver_finalize(fin_args(h, stage), h->nrhs, h->nb, 0, h->partials, mask, h->s);
 }
 
-// The iteration's x/r update and its finalize stage, in one launch where its
-// records are few.
-static hipError_t update_xr(wd_solver* h, const int* act) {
+// CG's x/r update and its finalize stage, in one launch where its records are
+// few.
+static hipError_t cg_update(wd_solver* h, const int* act) {
   const wd_prec P = h->prm.inner;
   const int records = blas_dot_records(h->geom, P);
-  const bool cg = h->kind == WD_SOLVER_CG;
-  const FinArgs fa = fin_args(h, cg ? FIN_CG_ITER : FIN_BICG_ITER);
+  const FinArgs fa = fin_args(h, FIN_CG_ITER);
   FinArgs in_kernel = fa;
   if (records > kFusedRecords) in_kernel.stage = -1;
-  hipError_t e = cg ? blas_cg_xr(h->geom, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), in_kernel, h->s)
-                    : blas_bicg_xr(h->geom, P, h->xh, h->rh, h->p, h->t, h->rt, h->sc, act, xr_records(h), in_kernel,
-                                   h->s);
+  const hipError_t e =
+      blas_cg_xr(h->geom, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), in_kernel, h->s);
   if (e != hipSuccess || in_kernel.stage >= 0) return e;
   return solver_finalize(fa, h->nrhs, records, 0, xr_records(h), act, h->s);
 }
@@ -214,14 +213,14 @@ static hipError_t pretune_inner(wd_solver* h) {
     d.a = -h->kappa * h->kappa;
     d.dot = dot;
     d.y = y;
-    d.partials = h->partials;
+    d.partials = dot == DOT_OX ? reinterpret_cast<double*>(h->to64.ptr) : h->partials;
     d.basis = kBasisUK;
     tune_dslash(h->g, P, d, h->s);
   };
   form(h->to, h->p, 1, 0, nullptr, DOT_NONE, nullptr);  // first half of M_hat p
   if (h->kind == WD_SOLVER_BICGSTAB) {
     form(h->v, h->to, 0, 0, &h->p, DOT_YO, &h->rt);
-    form(h->t, h->to, 0, 0, &h->p, DOT_OX, nullptr);
+    form(h->t, h->to, 0, 0, &h->p, DOT_OX, &h->rt);
   } else {
     form(h->t, h->to, 0, 0, &h->p, DOT_OO, nullptr);
     form(h->to, h->t, 1, 1, nullptr, DOT_NONE, nullptr);
@@ -231,24 +230,26 @@ static hipError_t pretune_inner(wd_solver* h) {
 }
 
 // One Krylov iteration in the inner precision, all active RHS.
-static hipError_t iteration_body(wd_solver* h) {
+// step: its place in the batch of iterations launched together.  BiCGstab's p
+// is up to date when an iteration begins (wd_solver_begin, solver_complete).
+static hipError_t iteration_body(wd_solver* h, int step) {
   const Geom& g = h->geom;
   const wd_prec P = h->prm.inner;
   const int* act = h->active;
   if (h->kind == WD_SOLVER_BICGSTAB) {
-    WD_TRY(blas_bicg_p(g, P, h->p, h->rh, h->v, h->sc, act, h->s));
     WD_TRY(mhat_into(h, P, h->v, h->p, h->to, 0, DOT_YO, &h->rt, act, 0, FIN_BICG_ALPHA));  // v = M p, <r~, v>
     WD_TRY(fin(h, FIN_BICG_ALPHA, act, true));
-    WD_TRY(blas_bicg_s(g, P, h->rh, h->v, h->sc, act, h->s));           // s = r - alpha v
-    WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, nullptr, act, 0, FIN_BICG_OMEGA));  // t = M s, <t,s>, |t|^2
-    WD_TRY(fin(h, FIN_BICG_OMEGA, act, true));
-    WD_TRY(update_xr(h, act));
+    WD_TRY(blas_bicg_s(g, P, h->rh, h->v, h->sc, act, h->s));  // s = r - alpha v
+    // t = M s and every dot product of the rest of the iteration
+    WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, &h->rt, act, 0, FIN_BICG_OMEGA, step));
+    WD_TRY(fin(h, FIN_BICG_OMEGA, act, true, step));
+    WD_TRY(blas_bicg_xrp(g, P, h->xh, h->rh, h->p, h->t, h->v, h->sc, h->fl, step, h->s));
   } else {
     // w = M p (|w|^2), q = M^dag w, x^ += alpha p, r^ -= alpha q
     WD_TRY(mhat_into(h, P, h->t, h->p, h->to, 0, DOT_OO, nullptr, act, 0, FIN_CG_ALPHA));
     WD_TRY(fin(h, FIN_CG_ALPHA, act, true));
     WD_TRY(mhat_into(h, P, h->v, h->t, h->to, 1, DOT_NONE, nullptr, act));
-    WD_TRY(update_xr(h, act));
+    WD_TRY(cg_update(h, act));
     // p = r^ + beta p where iteration goes on; an RHS that triggered a
     // reliable update is paused and takes this step after the update
     WD_TRY(blas_cg_p(g, P, h->p, h->rh, h->sc, act, h->s));
@@ -362,11 +363,14 @@ static bool fused_reseed(const wd_solver* h) {
   return h->kind == WD_SOLVER_BICGSTAB && h->prm.inner != WD_FP64;
 }
 
+// The update trigger of an RHS as read last (0, 1 or 2, see FlagSlot).
+static int trigger(const wd_solver* h, int k) { return h->h_fl[k * FL_COUNT + FL_RU] & 3; }
+
 static hipError_t reliable_update(wd_solver* h) {
   // the RHS that flagged an update (the device's rumask), listed for the dslash
   int n = 0;
   for (int k = 0; k < h->nrhs; ++k)
-    if (!h->done_rhs[k] && h->h_fl[k * FL_COUNT + FL_RU]) h->h_map[n++] = k;
+    if (!h->done_rhs[k] && trigger(h, k)) h->h_map[n++] = k;
   if (n > 0 && n < h->nrhs)
     WD_TRY(hipMemcpyAsync(h->rumap, h->h_map, sizeof(int) * n, hipMemcpyHostToDevice, h->s));
   else
@@ -558,6 +562,9 @@ wd_status wd_solver_begin(int32_t solver, const wd_gauge* g, double kappa, doubl
   // pick the inner-precision launch shapes of every form an iteration uses
   // before any graph capture
   if (e == hipSuccess) e = pretune_inner(h);
+  // BiCGstab's first search direction p = r^ (p = v = 0 before)
+  if (e == hipSuccess && solver == WD_SOLVER_BICGSTAB)
+    e = blas_bicg_p(h->geom, prm->inner, h->p, h->rh, h->v, h->sc, h->active, h->s);
   if (e == hipSuccess) e = read_flags(h);
   if (e != hipSuccess) {
     (void)hipHostFree(h->h_sc);
@@ -618,7 +625,7 @@ bool solver_finished(wd_solver* h) {
 // after it in the same batch leave it untouched and the result does not
 // depend on per_check.
 static hipError_t issue_body(wd_solver* h) {
-  for (int i = 0; i < h->per_check; ++i) WD_TRY(iteration_body(h));
+  for (int i = 0; i < h->per_check; ++i) WD_TRY(iteration_body(h, i));
   return hipSuccess;
 }
 
@@ -656,8 +663,7 @@ hipError_t solver_issue(wd_solver* h) {
 }
 
 // Wait for the issued iterations, account for them, and launch the reliable
-// update of the RHS that triggered one (CG: then their search-direction
-// update).  Iterations are counted on the device (FL_ITERS); a reliable
+// update of the RHS that triggered one, then their search-direction update.  Iterations are counted on the device (FL_ITERS); a reliable
 // update counts as one more (k + l).  The host waits for an update only where
 // it may end the solve of a right-hand side; the flags of the others come back
 // with the next iterations (one that converged all the same sits those out).
@@ -669,19 +675,21 @@ wd_status solver_complete(wd_solver* h) {
   h->loops += h->per_check;
   bool any_ru = false, may_end = false;
   for (int k = 0; k < h->nrhs; ++k) {
-    if (h->done_rhs[k] || !h->h_fl[k * FL_COUNT + FL_RU]) continue;
+    if (h->done_rhs[k] || !trigger(h, k)) continue;
     any_ru = true;
-    may_end |= h->h_fl[k * FL_COUNT + FL_RU] == 2;
+    may_end |= trigger(h, k) == 2;
   }
   if (any_ru) {
     e = reliable_update(h);
-    // CG: p = r^ + beta p for the updated RHS that iterate on (rumask)
-    if (e == hipSuccess && h->kind == WD_SOLVER_CG)
-      e = blas_cg_p(h->geom, h->prm.inner, h->p, h->rh, h->sc, h->rumask, h->s);
+    // the search direction from the new r^, for the RHS that iterate on (rumask)
+    if (e == hipSuccess)
+      e = h->kind == WD_SOLVER_CG
+              ? blas_cg_p(h->geom, h->prm.inner, h->p, h->rh, h->sc, h->rumask, h->s)
+              : blas_bicg_p(h->geom, h->prm.inner, h->p, h->rh, h->v, h->sc, h->rumask, h->s);
     if (e != hipSuccess) return hip_fail(e, "reliable update");
     ++h->loops;
     for (int k = 0; k < h->nrhs; ++k) {
-      if (h->done_rhs[k] || !h->h_fl[k * FL_COUNT + FL_RU]) continue;
+      if (h->done_rhs[k] || !trigger(h, k)) continue;
       ++h->rus[k];
       h->iters[k] = h->h_fl[k * FL_COUNT + FL_ITERS] + h->rus[k];
     }
