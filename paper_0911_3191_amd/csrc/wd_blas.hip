@@ -369,22 +369,37 @@ __global__ void __launch_bounds__(kBlock) k_reencode(int Vh, FieldView rh, Field
   block_sum_store<3>(d, partials + ((int64_t)rhs * gridDim.x + blockIdx.x) * kMaxDot);
 }
 
-// ---- finalize: partials -> scalars (one block per RHS) ---------------------------------
-// What bounds it is latency: the records of one right-hand side are summed by
-// one workgroup, with its scalars in flight meanwhile.  512 threads, wavefront
-// shuffles and one barrier: 8^4 3.0 -> 2.7 us, 24^3x32 with wave records
-// 5.3 -> 5.2 us on average (it waits for other XCDs' records).
+// ---- finalize: partials -> scalars ---------------------------------------------------
+// What bounds it is latency: the records come from other XCDs, and one CU has
+// only so many misses in flight.  The records of a right-hand side are summed
+// by gridDim.x workgroups, each a range of `chunk`; the last of them adds the
+// sums in order (see count_record) and runs the stage.  24^3x32, 864 records of
+// four wave records: 11.0 us with one workgroup for records of 8 doubles and 6.0
+// of 4, with seven 7.6 and 5.4.  8^4 (one workgroup) 2.7 us.
 template <int N>
-__global__ void __launch_bounds__(kFinBlock) k_finalize(int nb, int waves, const double* __restrict__ partials,
+__global__ void __launch_bounds__(kFinBlock) k_finalize(int nb, int chunk, int waves,
+                                                        const double* __restrict__ partials, double* sums,
                                                         const int* __restrict__ mask, FinArgs fa) {
-  const int rhs = blockIdx.x;
+  const int rhs = blockIdx.y, count = gridDim.x;
   if (mask && !mask[rhs]) return;
   const double* s = fa.sc + rhs * SC_COUNT;
   __shared__ double q[SC_COUNT];  // the scalars as they were
   const double own = threadIdx.x < SC_COUNT ? s[threadIdx.x] : 0.0;
   double r[N], v[kWideDot] = {};  // a stage reads the components that its records have
-  sum_partials<N>(partials + (int64_t)rhs * nb * (waves ? 4 : 1) * N, nb, waves != 0, r,
+  const int first = blockIdx.x * chunk;
+  sum_partials<N>(partials + ((int64_t)rhs * nb + first) * (waves ? 4 : 1) * N, min(chunk, nb - first), waves != 0, r,
                   [&] { if (threadIdx.x < SC_COUNT) q[threadIdx.x] = own; });
+  if (threadIdx.x >= 64) return;
+  if (count > 1) {
+    sums += (int64_t)rhs * count * N;
+    int last = 0;
+    if (threadIdx.x == 0) last = count_record<N>(r, sums + blockIdx.x * N, rhs, count, fa);
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+#pragma unroll
+    for (int k = 0; k < N; ++k) r[k] = 0.0;
+    if ((int)threadIdx.x < count) read_record<N>(sums + threadIdx.x * N, r);
+    wave_sum<N>(r);
+  }
   if (threadIdx.x != 0) return;
 #pragma unroll
   for (int k = 0; k < N; ++k) v[k] = r[k];
@@ -548,10 +563,20 @@ hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r6
   });
 }
 
-hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, const int* mask,
-                           hipStream_t s) {
-  if (fa.stage == FIN_BICG_OMEGA) k_finalize<kWideDot><<<nrhs, kFinBlock, 0, s>>>(nb, waves, partials, mask, fa);
-  else k_finalize<kMaxDot><<<nrhs, kFinBlock, 0, s>>>(nb, waves, partials, mask, fa);
+// Workgroups of k_finalize: by the records alone, so that every launch shape of
+// the kernel before it gives the same sums.  128 records to a workgroup and 64
+// take the same time (24^3x32: 7.6 and 5.4 us both).
+constexpr int kFinChunk = 128, kFinGroups = 32;
+static_assert(kFinGroups <= 64, "one sum a lane");
+
+hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, double* sums,
+                           const int* mask, hipStream_t s) {
+  int groups = !sums || nb <= kFusedRecords ? 1 : (nb + kFinChunk - 1) / kFinChunk;
+  if (groups > kFinGroups) groups = kFinGroups;
+  const int chunk = (nb + groups - 1) / groups;
+  const dim3 grid((nb + chunk - 1) / chunk, nrhs);
+  if (fa.stage == FIN_BICG_OMEGA) k_finalize<kWideDot><<<grid, kFinBlock, 0, s>>>(nb, chunk, waves, partials, sums, mask, fa);
+  else k_finalize<kMaxDot><<<grid, kFinBlock, 0, s>>>(nb, chunk, waves, partials, sums, mask, fa);
   return hipGetLastError();
 }
 

@@ -259,9 +259,10 @@ hipError_t blas_canon_norm2(const Geom& g, const double* canon, int nrhs, double
 hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r64, const Field* rt,
                          const int* mask, double* partials, hipStream_t s, bool set_rt = false);
 // fa.stage on the nb records per RHS of a launch (waves: wave records, four to
-// each, see DslashArgs::waves).
-hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, const int* mask,
-                           hipStream_t s);  // FIN_BICG_OMEGA: records of 8 doubles
+// each, see DslashArgs::waves).  FIN_BICG_OMEGA: records of 8 doubles.  sums: room
+// for nb records besides, which lets several workgroups share the sum; null: one.
+hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, double* sums,
+                           const int* mask, hipStream_t s);
 hipError_t solver_cg_tighten(int nrhs, double* sc, const int* fl, const int* mask, double tol,
                              hipStream_t s);
 hipError_t solver_init_flags(int nrhs, int* fl, int* active, int* rumask, double* sc, int counter, hipStream_t s);

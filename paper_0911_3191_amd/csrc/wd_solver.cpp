@@ -165,10 +165,11 @@ static double* xr_records(wd_solver* h) {
 static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash, int step = 0) {
   if (after_dslash) {
     if (h->finalized) return hipSuccess;
+    const bool aside = h->waves || stage == FIN_BICG_OMEGA;
     return solver_finalize(fin_args(h, stage, step), h->nrhs, h->nb_dslash, h->waves,
-                           h->waves || stage == FIN_BICG_OMEGA ? h->wave_records : h->partials, mask, h->s);
+                           aside ? h->wave_records : h->partials, aside ? h->partials : h->wave_records, mask, h->s);
   }
-  return solver_finalize(fin_args(h, stage), h->nrhs, h->nb, 0, h->partials, mask, h->s);
+  return solver_finalize(fin_args(h, stage), h->nrhs, h->nb, 0, h->partials, nullptr, mask, h->s);
 }
 
 // CG's x/r update and its finalize stage, in one launch where its records are
@@ -182,7 +183,9 @@ static hipError_t cg_update(wd_solver* h, const int* act) {
   const hipError_t e =
       blas_cg_xr(h->geom, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), in_kernel, h->s);
   if (e != hipSuccess || in_kernel.stage >= 0) return e;
-  return solver_finalize(fa, h->nrhs, records, 0, xr_records(h), act, h->s);
+  double* rec = xr_records(h);
+  double* to64 = reinterpret_cast<double*>(h->to64.ptr);
+  return solver_finalize(fa, h->nrhs, records, 0, rec, rec == to64 ? h->partials : to64, act, h->s);
 }
 
 #define WD_TRY(expr)                         \

@@ -120,7 +120,7 @@ def test_streaming_stores_keep_the_bits(prec, dims, monkeypatch):
 @pytest.mark.parametrize("dims", [(16, 16, 16, 16), (12, 10, 20, 28), (16, 16, 16, 32), (12, 16, 24, 30)])
 @pytest.mark.parametrize("solver", ["bicgstab", "cg"])
 @pytest.mark.parametrize("inner", ["fp64", "fp32", "f16"])
-def test_solves_on_both_sides_of_the_launch_rules(dims, solver, inner):
+def test_solves_on_both_sides_of_the_launch_rules(dims, solver, inner, monkeypatch):
     nrhs, kappa = 2, 0.12
     U = wdinputs.gauge_random(dims, 0.3, 97)
     s = Setup(dims, U, precs=tuple({"fp64", inner}))
@@ -128,7 +128,10 @@ def test_solves_on_both_sides_of_the_launch_rules(dims, solver, inner):
     bt = torch.from_numpy(np.ascontiguousarray(bs)).to(DEV)
     fn = wd.bicgstab_solve if solver == "bicgstab" else wd.cg_solve
     ref = None
-    for every, graph in ((1, False), (5, True)):
+    for every, graph, shape in ((1, False, None), (5, True, None), (2, False, "1,0,1"),
+                                (2, False, "1,0,1,0,0,0,0,0,256,1")):
+        if shape:  # block records and wave records
+            monkeypatch.setenv("WD_DSLASH_SHAPE", shape)
         params = wd.solve_params(tol=1e-10, inner=inner, delta=0.0 if inner == "fp64" else 0.1, nrhs=nrhs,
                                  use_graph=graph, check_every=every)
         x = torch.zeros_like(bt)
