@@ -99,11 +99,14 @@ def dslash_bytes_links(prec: str, nrhs: int, recon: int, temporal: bool, lt: int
 
 def bicgstab_iter_bytes(prec: str, nrhs: int) -> int:
     """One BiCGstab iteration for nrhs RHS, per site: 2 M_hat (4 dslash, the
-    second of each with the xpay read and the read of r~ for its dots) and
-    the BLAS-1 passes (s: 2R+1W, x/r/p: 5R+3W)."""
+    second of each with the xpay read and, for v, the <r~,v> read of r~) and
+    the BLAS-1 passes (p: 3R+1W, s: 2R+1W, x/r: 5R+2W).  The method's passes,
+    kept as the measure of a step whatever the library fuses: its own
+    iteration reads r~ for both dots and updates x, r and p in one pass
+    (5R+3W), 2 spinors of 25 less."""
     s = SPINOR_B[prec]
-    return (dslash_bytes(prec, nrhs) * 2 + dslash_bytes(prec, nrhs, 2) * 2  # + r~
-            + nrhs * s * (3 + 8))
+    return (dslash_bytes(prec, nrhs) * 2 + dslash_bytes(prec, nrhs, 1) * 2 + nrhs * s  # <r~,v>
+            + nrhs * s * (4 + 3 + 7))
 
 
 def ru_bytes(prec: str, nrhs: int) -> int:
