@@ -125,10 +125,53 @@ __global__ void __launch_bounds__(kBlock) k_bicg_s(int Vh, FieldView r, FieldVie
 }
 
 // x <- x + alpha p + omega s;  r <- s - omega t  (s lives in r);
+// partials: |r|^2, <r~, r>
+template <class S, bool SPLIT>
+__global__ void __launch_bounds__(kBlock) k_bicg_xr(int Vh, FieldView x, FieldView r, FieldView p, FieldView t,
+                                                    FieldView rt, const double* __restrict__ sc,
+                                                    const int* __restrict__ mask, double* __restrict__ partials,
+                                                    FinArgs fa) {
+  using R = typename S::real;
+  const int rhs = blockIdx.y;
+  if (mask && !mask[rhs]) return;
+  const int i = part_site<S, SPLIT>();
+  double d[3] = {0.0, 0.0, 0.0};
+  if (i < Vh) {
+    const double* s = sc + rhs * SC_COUNT;
+    const cx<R> al = cload<R>(s, SC_ALPHA), om = cload<R>(s, SC_OMEGA);
+    Part<S, SPLIT> X, Ss, P, T, Rt;
+    load_part<S, SPLIT>(x, rhs, i, X);
+    load_part<S, SPLIT>(r, rhs, i, Ss);
+    load_part<S, SPLIT>(p, rhs, i, P);
+    load_part<S, SPLIT>(t, rhs, i, T);
+    load_part<S, SPLIT>(rt, rhs, i, Rt);
+    R nn = 0, re = 0, im = 0;
+#pragma unroll
+    for (int n = 0; n < Part<S, SPLIT>::N; ++n) {
+      X.v[n] = X.v[n] + al * P.v[n] + om * Ss.v[n];
+      const cx<R> rn = Ss.v[n] - om * T.v[n];
+      Ss.v[n] = rn;
+      nn += rn.re * rn.re + rn.im * rn.im;
+      const cx<R> q = cmulc(Rt.v[n], rn);
+      re += q.re;
+      im += q.im;
+    }
+    store_part<S, SPLIT>(x, rhs, i, X);
+    store_part<S, SPLIT>(r, rhs, i, Ss);
+    d[0] = nn;
+    d[1] = re;
+    d[2] = im;
+  }
+  double* rec = partials + (int64_t)rhs * gridDim.x * kMaxDot;
+  if (fa.stage < 0) block_sum_store<3>(d, rec + blockIdx.x * kMaxDot);
+  else block_sum_finalize<3>(d, rec, blockIdx.x, gridDim.x, rhs, fa);
+}
+
+// x <- x + alpha p + omega s;  r <- s - omega t  (s lives in r);
 // p <- r + beta (p - omega v), unless the right-hand side pauses for a
 // reliable update, which re-seeds r first.  Eight fields moved; as an x/r update
 // with <r~, r> and |r|^2 and a p update it was eleven (and two launches more),
-// see FIN_BICG_OMEGA.  32^3x64, binary16, 12 RHS: 931 us (5.8 TB/s) instead of
+// see FIN_BICG_STEP.  32^3x64, binary16, 12 RHS: 931 us (5.8 TB/s) instead of
 // 888 + 488; the launch that now also reads r~ takes 721 instead of 604.
 template <class S, bool SPLIT>
 __global__ void __launch_bounds__(kBlock) k_bicg_xrp(int Vh, FieldView x, FieldView r, FieldView p, FieldView t,
@@ -484,13 +527,24 @@ hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double
 
 hipError_t blas_bicg_xrp(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field v, const double* sc,
                          const int* fl, int step, hipStream_t s) {
+  if (pr == WD_FP64) return hipErrorInvalidValue;  // blas_bicg_xr
   return by_prec(pr, [&](auto tag) {
     using S = decltype(tag);
-    by_split<S>(g, x.nrhs, [&](dim3 grid, auto split) {
-      k_bicg_xrp<S, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(t), fv(v), sc, fl,
-                                                                    step);
-    });
+    if constexpr (S::prec != WD_FP64)
+      by_split<S>(g, x.nrhs, [&](dim3 grid, auto split) {
+        k_bicg_xrp<S, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(t), fv(v), sc, fl,
+                                                                      step);
+      });
   });
+}
+
+hipError_t blas_bicg_xr(const Geom& g, Field x, Field r, Field p, Field t, Field rt, const double* sc,
+                        const int* mask, double* partials, const FinArgs& fa, hipStream_t s) {
+  by_split<SF64>(g, x.nrhs, [&](dim3 grid, auto split) {
+    k_bicg_xr<SF64, decltype(split)::value><<<grid, kBlock, 0, s>>>(g.Vh, fv(x), fv(r), fv(p), fv(t), fv(rt), sc,
+                                                                   mask, partials, fa);
+  });
+  return hipGetLastError();
 }
 
 hipError_t blas_cg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field q,
@@ -575,7 +629,7 @@ hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const
   if (groups > kFinGroups) groups = kFinGroups;
   const int chunk = (nb + groups - 1) / groups;
   const dim3 grid((nb + chunk - 1) / chunk, nrhs);
-  if (fa.stage == FIN_BICG_OMEGA) k_finalize<kWideDot><<<grid, kFinBlock, 0, s>>>(nb, chunk, waves, partials, sums, mask, fa);
+  if (fa.stage == FIN_BICG_STEP) k_finalize<kWideDot><<<grid, kFinBlock, 0, s>>>(nb, chunk, waves, partials, sums, mask, fa);
   else k_finalize<kMaxDot><<<grid, kFinBlock, 0, s>>>(nb, chunk, waves, partials, sums, mask, fa);
   return hipGetLastError();
 }

@@ -29,7 +29,7 @@ hipError_t launch_dslash_ex(const wd_gauge* g, wd_prec prec, const DslashArgs& d
   if (d.basis != kBasisDR && d.basis != kBasisUK) return hipErrorInvalidValue;
   if (d.basis == kBasisDR && d.xpay && d.dot != DOT_NONE) return hipErrorInvalidValue;
   if (d.rhs_map && (d.n_map < 1 || d.n_map > d.out.nrhs)) return hipErrorInvalidValue;
-  if (d.xpay && (d.dot == DOT_YO || d.dot == DOT_OX) && !d.y) return hipErrorInvalidValue;
+  if (d.xpay && (d.dot == DOT_YO || (d.dot == DOT_OX && prec != WD_FP64)) && !d.y) return hipErrorInvalidValue;
   if (d.dot == DOT_RES && (prec != WD_FP64 || !d.xpay || !d.y || d.dagger)) return hipErrorInvalidValue;
   if (d.dot == DOT_RES_ENC &&
       (prec != WD_FP64 || !d.xpay || !d.y || d.dagger || d.basis != kBasisUK || !d.enc_rh || !d.enc_xh ||

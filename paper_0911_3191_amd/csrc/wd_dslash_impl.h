@@ -1056,8 +1056,8 @@ __device__ __forceinline__ void hop_pair(Spinor<typename S::real> (&acc)[NR], co
 // out = D in, or out = x + a * D in (XPAY), optionally followed by per-block
 // FP64 partial dot products of the result (DOT):
 //   DOT_YO: <y, out>                 (complex; BiCGstab <r~, v>)
-//   DOT_OX: <out, x>, |out|^2, <y, out>, <y, x>, |x|^2 of the stored out
-//                                    (BiCGstab: t = out, s = x, r~ = y)
+//   DOT_OX: <out, x>, |out|^2        (BiCGstab <t, s>, <t, t> with x = s); below
+//           FP64 also <y, out>, <y, x>, |x|^2 with y = r~, all of the stored out
 //   DOT_OO: |out|^2                  (CG |M p|^2)
 //   DOT_RES: out = y - (x + a * D in), |out|^2 (FP64 residual b_hat - M_hat x)
 //   DOT_RES_ENC: r = y - (x + a * D in) re-encoded in format S2 into enc.rh
@@ -1139,7 +1139,7 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
 #pragma unroll
         for (int c = 0; c < 3; ++c) acc.v[s][c] = b.v[s][c] - acc.v[s][c];
     }
-    if constexpr (DOT == DOT_OX) {
+    if constexpr (DOT == DOT_OX && S::prec != WD_FP64) {
       Spinor<R> back;  // the dots see the stored value
       if (g.out_nt) {
         asm volatile("; streaming stores");
@@ -1241,6 +1241,22 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         d[1] = im;
       }
       sum_store<2, WAVE>(d, part, pid, nb, r, enc.fin);
+    } else if constexpr (DOT == DOT_OX && S::prec == WD_FP64) {
+      double d[3] = {0.0, 0.0, 0.0};
+      if (valid) {
+        R re = 0, im = 0, nn = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            acc_cdotc(re, im, acc.v[s][c], x.v[s][c]);
+            acc_norm(nn, acc.v[s][c]);
+          }
+        d[0] = re;
+        d[1] = im;
+        d[2] = nn;
+      }
+      sum_store<3, WAVE>(d, part, pid, nb, r, enc.fin);
     } else if constexpr (DOT == DOT_OX) {
       double d[kWideDot] = {};
       if (valid) {

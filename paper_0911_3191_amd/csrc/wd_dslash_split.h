@@ -215,16 +215,13 @@ __device__ __forceinline__ void decode_raw(const RawSite<S>& q, Spinor<typename 
 }
 
 // Wavefronts per SIMD that the register count has to allow: three workgroups
-// per CU (FP64 with one hop per wavefront: two).  With the dots of DOT_OX the
-// FP64 finisher holds three spinors; the sizes that take this shape have less
-// than one workgroup per CU, so one may take the registers of both: without
-// the spills the launch takes 10.4 us instead of 14.0 on 8^4.
-template <class S, int HPW, int DOT>
-constexpr int split_waves() { return S::prec == WD_FP64 ? (HPW == 2 ? 3 : (DOT == DOT_OX ? 2 : 4)) : 6; }
+// per CU (FP64 with one hop per wavefront: two).
+template <class S, int HPW>
+constexpr int split_waves() { return S::prec == WD_FP64 ? (HPW == 2 ? 3 : 4) : 6; }
 
 // HPW: hops per wavefront (2: both of one direction, four wavefronts).
 template <class S, bool DAGGER, bool XPAY, int DOT, int RECON, int BASIS, int HPW, class S2 = S>
-__global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW, DOT>())) dslash_split_kernel(DslashGeom g, const char* __restrict__ links,
+__global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW>())) dslash_split_kernel(DslashGeom g, const char* __restrict__ links,
                                                                   FieldView out, FieldView in, FieldView xs,
                                                                   FieldView ys, typename S::real a, int p,
                                                                   const int* __restrict__ sel,
@@ -326,7 +323,7 @@ __global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW, DOT>())) dslas
   }
   // the finishing wavefront's x and y loads are in flight across the barrier
   // (FP64: only x, the registers of both would cost a workgroup per CU)
-  constexpr bool NEEDS_Y = DOT == DOT_YO || DOT == DOT_OX || DOT == DOT_RES || DOT == DOT_RES_ENC;
+  constexpr bool NEEDS_Y = DOT == DOT_YO || (DOT == DOT_OX && S::prec != WD_FP64) || DOT == DOT_RES || DOT == DOT_RES_ENC;
   RawSite<S> xr, yr;
   if (hop == 0) {
     if constexpr (XPAY) load_raw<S>(xs, r, cb, xr);

@@ -108,7 +108,43 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
       s[SC_ALPHA + 1] = a.im;
       break;
     }
-    case FIN_BICG_OMEGA: {
+    case FIN_BICG_OMEGA: {  // omega = <t, s> / <t, t>
+      if (v[2] == 0.0 && v[0] == 0.0 && v[1] == 0.0) {  // as in FIN_BICG_STEP
+        s[SC_OMEGA] = 1.0;
+        s[SC_OMEGA + 1] = 0.0;
+        break;
+      }
+      if (!(v[2] > 0.0) || !isfinite(v[2])) {
+        f[FL_BREAK] = stage + 1;
+        active[rhs] = 0;
+        break;
+      }
+      s[SC_OMEGA] = v[0] / v[2];
+      s[SC_OMEGA + 1] = v[1] / v[2];
+      break;
+    }
+    case FIN_BICG_ITER: {  // |r^|^2, <r~, r^>: beta, reliable-update trigger
+      const double rn = sqrt(v[0]);
+      if (!isfinite(rn) || !(omega0.re * omega0.re + omega0.im * omega0.im > 0.0)) {
+        f[FL_BREAK] = stage + 1;
+        active[rhs] = 0;
+        break;
+      }
+      s[SC_RHOP] = rho0.re;
+      s[SC_RHOP + 1] = rho0.im;
+      s[SC_RHO] = v[1];
+      s[SC_RHO + 1] = v[2];
+      s[SC_R2] = v[0];
+      store_beta(s, {v[1], v[2]}, rho0, alpha0, omega0);
+      const double mmax = fa.restart ? q[SC_MMAX] : fmax(q[SC_MMAX], rn);
+      s[SC_MMAX] = mmax;
+      const int ru = rn <= stop ? 2 : (rn < fa.delta * mmax ? 1 : 0);
+      f[FL_RU] = ru;
+      rumask[rhs] = ru != 0;
+      if (ru) active[rhs] = 0;  // paused until the host has run the update
+      break;
+    }
+    case FIN_BICG_STEP: {
       // v = <t, s>, |t|^2, <r~, t>, <r~, s>, |s|^2 of the stored t and s:
       // omega = <t, s> / <t, t>, and for r = s - omega t at once rho = <r~, r>,
       // beta and |r|^2, so that one update can take x, r and p
@@ -121,7 +157,7 @@ __device__ __forceinline__ void apply_stage(const FinArgs& fa, int rhs, const do
         // reliable update follows)
         om = one;
       } else if (!(t2 > 0.0) || !isfinite(t2)) {
-        f[FL_BREAK] = stage + 1;
+        f[FL_BREAK] = FIN_BICG_OMEGA + 1;
         active[rhs] = 0;
         break;
       } else {

@@ -81,14 +81,15 @@ enum ScalarSlot {
 // FL_ITERS counts the inner iterations an RHS has started, on the device, so
 // that several iterations can run between two reads of the flags by the host.
 // FL_RU: 0, 1 (the residual has dropped by delta) or 2 (it may have converged);
-// BiCGstab adds 4 * (step + 1) while the update of iteration `step` of its
+// FIN_BICG_STEP adds 4 * (step + 1) while the update of iteration `step` of its
 // batch is to run.
 enum FlagSlot { FL_RU = 0, FL_BREAK = 1, FL_CONV = 2, FL_ITERS = 3, FL_COUNT = 4 };
 enum FinStage {
   FIN_B2, FIN_TRUE, FIN_RHO, FIN_BICG_INIT, FIN_BICG_ALPHA, FIN_BICG_OMEGA,
   FIN_BICG_ITER, FIN_CG_INIT, FIN_CG_ALPHA, FIN_CG_ITER, FIN_CG_RHO,
   FIN_TRUE_RHO,  // FIN_TRUE on v[0], then FIN_RHO on v[1..3] where iteration goes on
-  FIN_TRUE_INIT  // FIN_TRUE on v[0], then FIN_BICG_INIT on v[1..3] where iteration goes on
+  FIN_TRUE_INIT, // FIN_TRUE on v[0], then FIN_BICG_INIT on v[1..3] where iteration goes on
+  FIN_BICG_STEP  // FIN_BICG_OMEGA and FIN_BICG_ITER at once, from the dots of s and t (inner formats below FP64)
 };
 // A finalize stage: what it does and where the scalars live.  restart = 1
 // (defect correction): the update trigger compares |r^| with the residual the
@@ -110,7 +111,7 @@ struct FinArgs {
 constexpr int kFusedRecords = 128;
 
 // ---- launchers (defined in the .hip files; all asynchronous on `s`) -------------
-constexpr int kMaxDotHost = 4;  // doubles per partial record (DOT_OX: 8)
+constexpr int kMaxDotHost = 4;  // doubles per partial record (DOT_OX below FP64: 8)
 // DOT_RES (FP64 only): out = y - (xpay + a D in), the residual of a reliable
 // update, with |out|^2 partials.  DOT_RES_ENC (FP64, UKQCD basis): the same
 // residual r is not stored in FP64 but re-encoded straight into the inner
@@ -234,13 +235,16 @@ hipError_t blas_bicg_p(const Geom& g, wd_prec pr, Field p, Field r, Field v, con
                        const int* mask, hipStream_t s);
 hipError_t blas_bicg_s(const Geom& g, wd_prec pr, Field r, Field v, const double* sc,
                        const int* mask, hipStream_t s);
-// Partial records per RHS that blas_cg_xr writes (up to four times those of
-// the other kernels).
+// Partial records per RHS that blas_cg_xr and blas_bicg_xr write (up to four
+// times those of the other kernels).
 int blas_dot_records(const Geom& g, wd_prec p);
-// The x, r and p updates of iteration `step`, for the RHS whose FL_RU names it
+// FP64: the x and r updates and the sums of the new r.  The other formats: the x,
+// r and p updates of iteration `step`, for the RHS whose FL_RU names it
 // (p: those that do not pause for a reliable update).
 hipError_t blas_bicg_xrp(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field t, Field v, const double* sc,
                          const int* fl, int step, hipStream_t s);
+hipError_t blas_bicg_xr(const Geom& g, Field x, Field r, Field p, Field t, Field rt, const double* sc,
+                        const int* mask, double* partials, const FinArgs& fa, hipStream_t s);
 hipError_t blas_cg_xr(const Geom& g, wd_prec pr, Field x, Field r, Field p, Field q,
                       const double* sc, const int* mask, double* partials, const FinArgs& fa, hipStream_t s);
 hipError_t blas_cg_p(const Geom& g, wd_prec pr, Field p, Field r, const double* sc,
@@ -259,7 +263,7 @@ hipError_t blas_canon_norm2(const Geom& g, const double* canon, int nrhs, double
 hipError_t blas_reencode(const Geom& g, wd_prec pr, Field rh, Field xh, Field r64, const Field* rt,
                          const int* mask, double* partials, hipStream_t s, bool set_rt = false);
 // fa.stage on the nb records per RHS of a launch (waves: wave records, four to
-// each, see DslashArgs::waves).  FIN_BICG_OMEGA: records of 8 doubles.  sums: room
+// each, see DslashArgs::waves).  FIN_BICG_STEP: records of 8 doubles.  sums: room
 // for nb records besides, which lets several workgroups share the sum; null: one.
 hipError_t solver_finalize(const FinArgs& fa, int nrhs, int nb, int waves, const double* partials, double* sums,
                            const int* mask, hipStream_t s);

@@ -12,7 +12,7 @@ namespace wd {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr int kMaxDot = 4;  // doubles per partial record (DOT_OX: kWideDot)
+constexpr int kMaxDot = 4;  // doubles per partial record (DOT_OX below FP64: kWideDot)
 constexpr int kWideDot = 8;
 template <int N>
 constexpr int kRecord = N > kMaxDot ? kWideDot : kMaxDot;  // record of N components

@@ -113,7 +113,7 @@ static hipError_t launch_dot(wd_solver* h, wd_prec prec, DslashArgs& d, int stag
   const bool hi = d.in.ptr == h->to64.ptr || d.out.ptr == h->to64.ptr || (d.xpay && d.xpay->ptr == h->to64.ptr);
   h->wave_records = reinterpret_cast<double*>(hi ? h->to.ptr : h->to64.ptr);
   d.wave_partials = h->wave_records;
-  if (d.dot == DOT_OX) d.partials = h->wave_records;  // records of 8 doubles
+  if (stage == FIN_BICG_STEP) d.partials = h->wave_records;  // records of 8 doubles
   d.waves = &h->waves;
   d.fin = fin_args(h, stage, step);
   d.finalized = &h->finalized;
@@ -153,7 +153,7 @@ static hipError_t mhat_into(wd_solver* h, wd_prec prec, const Field& out, const 
   return dslash_into(h, prec, out, tmp_odd, 0, dagger, &in, -h->kappa * h->kappa, dot, y, mask, n_map, stage, step);
 }
 
-// Records of CG's x/r update: more than h->partials has room for
+// Records of the x/r update (CG, FP64 BiCGstab): more than h->partials has room for
 // where it splits sites over threads; the FP64 odd temporary is free then.
 static double* xr_records(wd_solver* h) {
   return blas_dot_records(h->geom, h->prm.inner) <= h->nb ? h->partials : reinterpret_cast<double*>(h->to64.ptr);
@@ -165,25 +165,27 @@ static double* xr_records(wd_solver* h) {
 static hipError_t fin(wd_solver* h, int stage, const int* mask, bool after_dslash, int step = 0) {
   if (after_dslash) {
     if (h->finalized) return hipSuccess;
-    const bool aside = h->waves || stage == FIN_BICG_OMEGA;
+    const bool aside = h->waves || stage == FIN_BICG_STEP;
     return solver_finalize(fin_args(h, stage, step), h->nrhs, h->nb_dslash, h->waves,
                            aside ? h->wave_records : h->partials, aside ? h->partials : h->wave_records, mask, h->s);
   }
   return solver_finalize(fin_args(h, stage), h->nrhs, h->nb, 0, h->partials, nullptr, mask, h->s);
 }
 
-// CG's x/r update and its finalize stage, in one launch where its records are
-// few.
-static hipError_t cg_update(wd_solver* h, const int* act) {
+// The x/r update (CG, FP64 BiCGstab) and its finalize stage, in one launch
+// where its records are few.
+static hipError_t xr_update(wd_solver* h, const int* act) {
   const wd_prec P = h->prm.inner;
+  const bool cg = h->kind == WD_SOLVER_CG;
   const int records = blas_dot_records(h->geom, P);
-  const FinArgs fa = fin_args(h, FIN_CG_ITER);
+  const FinArgs fa = fin_args(h, cg ? FIN_CG_ITER : FIN_BICG_ITER);
   FinArgs in_kernel = fa;
   if (records > kFusedRecords) in_kernel.stage = -1;
-  const hipError_t e =
-      blas_cg_xr(h->geom, P, h->xh, h->rh, h->p, h->v, h->sc, act, xr_records(h), in_kernel, h->s);
-  if (e != hipSuccess || in_kernel.stage >= 0) return e;
   double* rec = xr_records(h);
+  const hipError_t e =
+      cg ? blas_cg_xr(h->geom, P, h->xh, h->rh, h->p, h->v, h->sc, act, rec, in_kernel, h->s)
+         : blas_bicg_xr(h->geom, h->xh, h->rh, h->p, h->t, h->rt, h->sc, act, rec, in_kernel, h->s);
+  if (e != hipSuccess || in_kernel.stage >= 0) return e;
   double* to64 = reinterpret_cast<double*>(h->to64.ptr);
   return solver_finalize(fa, h->nrhs, records, 0, rec, rec == to64 ? h->partials : to64, act, h->s);
 }
@@ -216,7 +218,7 @@ static hipError_t pretune_inner(wd_solver* h) {
     d.a = -h->kappa * h->kappa;
     d.dot = dot;
     d.y = y;
-    d.partials = dot == DOT_OX ? reinterpret_cast<double*>(h->to64.ptr) : h->partials;
+    d.partials = dot == DOT_OX ? reinterpret_cast<double*>(h->to64.ptr) : h->partials;  // room for wide records
     d.basis = kBasisUK;
     tune_dslash(h->g, P, d, h->s);
   };
@@ -243,16 +245,26 @@ static hipError_t iteration_body(wd_solver* h, int step) {
     WD_TRY(mhat_into(h, P, h->v, h->p, h->to, 0, DOT_YO, &h->rt, act, 0, FIN_BICG_ALPHA));  // v = M p, <r~, v>
     WD_TRY(fin(h, FIN_BICG_ALPHA, act, true));
     WD_TRY(blas_bicg_s(g, P, h->rh, h->v, h->sc, act, h->s));  // s = r - alpha v
+    if (P == WD_FP64) {
+      // t = M s, <t, s>, |t|^2; then rho and |r|^2 are sums over the new r: taken
+      // from s and t like below, they would round 1.3-10 times coarser than that
+      WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, nullptr, act, 0, FIN_BICG_OMEGA));
+      WD_TRY(fin(h, FIN_BICG_OMEGA, act, true));
+      WD_TRY(xr_update(h, act));
+      // an RHS that pauses for an update takes this step after it
+      WD_TRY(blas_bicg_p(g, P, h->p, h->rh, h->v, h->sc, act, h->s));
+      return hipSuccess;
+    }
     // t = M s and every dot product of the rest of the iteration
-    WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, &h->rt, act, 0, FIN_BICG_OMEGA, step));
-    WD_TRY(fin(h, FIN_BICG_OMEGA, act, true, step));
+    WD_TRY(mhat_into(h, P, h->t, h->rh, h->to, 0, DOT_OX, &h->rt, act, 0, FIN_BICG_STEP, step));
+    WD_TRY(fin(h, FIN_BICG_STEP, act, true, step));
     WD_TRY(blas_bicg_xrp(g, P, h->xh, h->rh, h->p, h->t, h->v, h->sc, h->fl, step, h->s));
   } else {
     // w = M p (|w|^2), q = M^dag w, x^ += alpha p, r^ -= alpha q
     WD_TRY(mhat_into(h, P, h->t, h->p, h->to, 0, DOT_OO, nullptr, act, 0, FIN_CG_ALPHA));
     WD_TRY(fin(h, FIN_CG_ALPHA, act, true));
     WD_TRY(mhat_into(h, P, h->v, h->t, h->to, 1, DOT_NONE, nullptr, act));
-    WD_TRY(cg_update(h, act));
+    WD_TRY(xr_update(h, act));
     // p = r^ + beta p where iteration goes on; an RHS that triggered a
     // reliable update is paused and takes this step after the update
     WD_TRY(blas_cg_p(g, P, h->p, h->rh, h->sc, act, h->s));
