@@ -284,7 +284,8 @@ typedef struct {
                           them; WD_FP64 gives the plain double-precision solver */
   double delta;        /* reliable-update trigger of Algorithm 2: update when |r^| < delta *
                           max|r^| since the last update; 0 <= delta < 1 (0: update only to
-                          confirm convergence) */
+                          confirm convergence, for which BiCGstab below FP64 also takes a
+                          step that leaves less than FP32 rounding of the residual, 6e-8) */
   int32_t nrhs;        /* right-hand sides solved together, 1..64 (one multi-RHS dslash per hop) */
   int32_t use_graph;   /* 1: the iteration body is captured once as a hipGraph and replayed
                           (needs a non-NULL stream); a solve shorter than 12 batches of

@@ -1097,6 +1097,9 @@ __device__ __forceinline__ void acc_norm(T& nn, const cx<R>& u) {
   nn = fmad(T(u.im), T(u.im), nn);
 }
 
+template <class R>
+__device__ __forceinline__ cx<double> to_double(const cx<R>& u) { return {(double)u.re, (double)u.im}; }
+
 // Per right-hand side after the hops: xpay, residual, store (or re-encode)
 // and the fused FP64 partial dot products of one workgroup.  Every thread of
 // the block calls it for the same r (the reductions synchronise the block).
@@ -1263,25 +1266,19 @@ __device__ __forceinline__ void finish_rhs(const DslashGeom& g, Spinor<typename 
         Spinor<R> y;
         if constexpr (WAVE) y = *yw;
         else load_spinor<S>(ys, r, cb, y);
-        R re = 0, im = 0, nn = 0, yre = 0, yim = 0, xre = 0, xim = 0, xx = 0;
+        // rho and |r|^2 are differences of these sums (FIN_BICG_STEP): FP64 from
+        // the first product on, or they would round coarser than sums over r
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            acc_cdotc(re, im, acc.v[s][c], x.v[s][c]);
-            acc_norm(nn, acc.v[s][c]);
-            acc_cdotc(yre, yim, y.v[s][c], acc.v[s][c]);
-            acc_cdotc(xre, xim, y.v[s][c], x.v[s][c]);
-            acc_norm(xx, x.v[s][c]);
+            const cx<double> u = to_double(acc.v[s][c]), v = to_double(x.v[s][c]), w = to_double(y.v[s][c]);
+            acc_cdotc(d[0], d[1], u, v);
+            acc_norm(d[2], u);
+            acc_cdotc(d[3], d[4], w, u);
+            acc_cdotc(d[5], d[6], w, v);
+            acc_norm(d[7], v);
           }
-        d[0] = re;
-        d[1] = im;
-        d[2] = nn;
-        d[3] = yre;
-        d[4] = yim;
-        d[5] = xre;
-        d[6] = xim;
-        d[7] = xx;
       }
       sum_store<8, WAVE>(d, partials + (int64_t)r * nb * kWideDot, pid, nb, r, enc.fin);
     } else {

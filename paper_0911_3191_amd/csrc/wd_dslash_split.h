@@ -215,13 +215,19 @@ __device__ __forceinline__ void decode_raw(const RawSite<S>& q, Spinor<typename 
 }
 
 // Wavefronts per SIMD that the register count has to allow: three workgroups
-// per CU (FP64 with one hop per wavefront: two).
-template <class S, int HPW>
-constexpr int split_waves() { return S::prec == WD_FP64 ? (HPW == 2 ? 3 : 4) : 6; }
+// per CU (FP64 with one hop per wavefront: two).  The FP64 sums of DOT_OX take
+// more registers: FP32 spills 68 at six and takes two workgroups (6 spilled; a
+// 24^3x32 solve 8.4 ms); the 16-bit formats spill 20 and are still faster
+// with three (6.2 ms instead of 6.4 with none spilled).
+template <class S, int HPW, int DOT>
+constexpr int split_waves() {
+  if (S::prec == WD_FP64) return HPW == 2 ? 3 : 4;
+  return S::prec == WD_FP32 && DOT == DOT_OX ? 4 : 6;
+}
 
 // HPW: hops per wavefront (2: both of one direction, four wavefronts).
 template <class S, bool DAGGER, bool XPAY, int DOT, int RECON, int BASIS, int HPW, class S2 = S>
-__global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW>())) dslash_split_kernel(DslashGeom g, const char* __restrict__ links,
+__global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW, DOT>())) dslash_split_kernel(DslashGeom g, const char* __restrict__ links,
                                                                   FieldView out, FieldView in, FieldView xs,
                                                                   FieldView ys, typename S::real a, int p,
                                                                   const int* __restrict__ sel,

@@ -50,7 +50,7 @@ def start(kappa, inner, **kw):
     return U, bs, s, wd.Solver("bicgstab", s.gauge, kappa, torch.zeros_like(bt), bt, params, ws)
 
 
-@pytest.mark.parametrize("inner,unit", [("fp64", 2.0 ** -53)])
+@pytest.mark.parametrize("inner,unit", [("fp64", 2.0 ** -53), ("fp32", 2.0 ** -24)])
 def test_residual_norm_of_a_steep_step(inner, unit):
     kappa = 0.007
     U, bs, _, h = start(kappa, inner, delta=0.0)
@@ -64,7 +64,7 @@ def test_residual_norm_of_a_steep_step(inner, unit):
         assert abs(got[k] / r ** 2 - 1) <= bound, k
 
 
-@pytest.mark.parametrize("inner", ["fp64"])
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "i16", "f16"])
 @pytest.mark.parametrize("restart,delta", [(False, 0.0), (True, 1e-9)])
 def test_a_steep_step_brings_no_update_of_its_own(inner, restart, delta):
     """|r| falls to 4e-8 |r0| and to 2e-4 |s|: above tol, and above delta |r0|."""
