@@ -101,25 +101,33 @@ bool streams_output(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
 
 // Where one wavefront per hop (wd_dslash_split.h) replaces the searched
 // shapes: by the bytes of the launch (links once, every right-hand side's
-// input and output), so that the choice needs no timing.  It wins while the
+// input and output), the same in every process.  (The search still runs and is
+// recorded for the key: launches that the split kernel is not built for use
+// it.)  It wins while the
 // launch stays in the 256 MB last-level cache, where the one-thread kernels
 // wait on latency with the bandwidth unused, and loses once HBM sets the
 // pace.  Measured, best one-thread shape against it in microseconds: FP64
-// 24^3x32 (255 MB) 61 / 45, 24^3x48 (382 MB) 84 / 88, 16^3x32 with 12
-// right-hand sides (352 MB) 121 / 157; FP32 32^3x32 (302 MB) 60 / 55, 32^3x64
-// (604 MB) 120 / 129; one 16-bit right-hand side 32^3x32 (155 MB) 36 / 29,
-// 32^3x64 (310 MB) 64 / 71.  Several 16-bit right-hand sides share their links
-// in the one-thread kernels, and the rebuilt third row is a large part of
-// their work: level from about 131,072 site right-hand sides (16^3x32 with 2:
-// 10.4 / 10.3, 20x14x10x18 with 5: 10.2 / 10.6, with 12: 17.0 / 18.5).
+// 24^3x32 (255 MB) 61 / 45, 24^3x48 (382 MB) 84 / 88, 16^3x32 with 8
+// right-hand sides (252 MB) 96 / 63, with 12 (352 MB) 121 / 157; FP32 32^3x32
+// (302 MB) 60 / 55, 32^3x64 (604 MB) 120 / 129, 24^3x32 with 4 (255 MB)
+// 70 / 55, with 5 (297 MB) 80 / 91; one 16-bit right-hand side 32^3x32 (155 MB)
+// 36 / 29, 32^3x64 (310 MB) 64 / 71.  Several 16-bit right-hand sides share
+// their links in the one-thread kernels, and the rebuilt third row is a large
+// part of their work, of the shorter binary16 arithmetic above all.  Binary16:
+// 16^4 with 2 (65,536 site right-hand sides) 7.4 / 7.3, with 3 (98,304)
+// 9.9 / 9.8, with 4 (131,072) 10.5 / 11.5; 20x14x10x18 with 4 (100,800)
+// 9.3 / 9.6; 12^3x24 with 5 (103,680) 9.0 / 9.4.  int16: 16^4 with 3 10.4 / 9.8,
+// with 4 11.8 / 12.0; 16^3x32 with 2 (131,072) 11.5 / 10.8; 20x14x10x18 with 5
+// (126,000) 10.8 / 10.9.
 bool split_pays(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
   const int64_t Vh = g->geom.Vh, n = launch_rhs(d), bytes = launch_bytes(g, prec, d);
-  if (is_half(prec)) return n == 1 ? bytes <= (200 << 20) : Vh * n <= (1 << 17);
+  if (is_half(prec) && n == 1) return bytes <= (200 << 20);
+  if (is_half(prec)) return Vh * n <= (prec == WD_HALF_F16 ? 3 << 15 : 4 << 15);
   // the residual forms end in long FP64 epilogues, which the split kernel's one
   // finishing wavefront takes alone: 8^4 11.0 / 7.1, 24^3x32 64.8 / 74.3
   const bool residual = d.xpay && (d.dot == DOT_RES || d.dot == DOT_RES_ENC || d.dot == DOT_ENC);
   if (residual && Vh * n > (1 << 16)) return false;
-  return bytes <= (prec == WD_FP64 ? (256 << 20) : (300 << 20));
+  return bytes <= (prec == WD_FP32 && n == 1 ? (300 << 20) : (256 << 20));
 }
 
 LaunchCfg default_cfg(int nrhs) { return LaunchCfg{nrhs == 1 ? 1 : 2, 256}; }
