@@ -89,14 +89,19 @@ int64_t launch_bytes(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
 // Whether a launch's output stores are marked streaming (evicted first), so
 // that neighbours and links keep the caches.  It pays once the launch is well
 // past the 256 MB last-level cache; below, the next launch would have found the
-// output there.  Measured, plain / streaming in microseconds: one right-hand
-// side FP64 48^3x96 1286 / 1228, FP32 32^3x96 (906 MB) 182 / 176, binary16
-// 48^3x64 (1.05 GB) 226 / 211, 40^3x64 (606 MB) 126 / 129, FP32 32^3x64 (604 MB)
-// 122 / 126; twelve binary16 24^3x32 (318 MB) 119 / 104, FP64 32^3x64 2044 /
-// 1938, FP32 48^3x96 4855 / 4607; three binary16 24^3x32 (111 MB) 33 / 35.
+// output there.  Measured, plain / streaming in microseconds, each with its
+// best shape: one right-hand side FP64 48^3x96 1286 / 1228, FP32 32^3x96 (906 MB)
+// 182 / 176, binary16 48^3x64 (1.05 GB) 226 / 211, 40^3x64 (606 MB) 126 / 129,
+// FP32 32^3x64 (604 MB) 122 / 126.  Several, below the line: binary16 32^3x32
+// with 3 (264 MB) 54 / 64, 24^3x32 with 10 (272 MB) 86 / 89, int16 the same
+// 89 / 92; above it: FP32 24^3x32 with 5 (297 MB) 95 / 80, 24^3x48 with 3 (318 MB)
+// 96 / 81, binary16 32^3x32 with 4 (319 MB) 86 / 80, 24^3x32 with 12 (319 MB)
+// 117 / 104, int16 the same 120 / 108, FP64 24^3x32 with 2, 3, 4, 5 (340-594 MB)
+// 98 / 97, 142 / 136, 170 / 165, 204 / 197, FP64 32^3x64 with 12 2044 / 1938,
+// FP32 48^3x96 4855 / 4607.
 bool streams_output(const wd_gauge* g, wd_prec prec, const DslashArgs& d) {
   const int64_t mb = launch_bytes(g, prec, d) >> 20;
-  return launch_rhs(d) == 1 ? mb >= 800 : mb >= 290;
+  return launch_rhs(d) == 1 ? mb >= 800 : mb >= 280;
 }
 
 // Where one wavefront per hop (wd_dslash_split.h) replaces the searched
