@@ -63,7 +63,7 @@
  *                         (RHS slots per thread, RHS-group order, y-sub-slabs,
  *                         cache hints, workgroups per CU cap, LDS staging,
  *                         binary16 RHS loop, workgroup size, one wavefront per
- *                         hop: small launches, the other fields do not apply)
+ *                         hop: small launches, of the other fields only out_nt applies)
  */
 #ifndef WD_H
 #define WD_H

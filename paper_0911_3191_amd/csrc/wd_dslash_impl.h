@@ -1851,12 +1851,12 @@ static bool lds_usable(const wd_gauge* gg, wd_prec prec, const LaunchCfg& c) {
 
 // One wavefront per hop (wd_dslash_split.h).
 template <class S, int BASIS>
-static void launch_split(const wd_gauge* gg, const DslashArgs& d, hipStream_t s);
+static void launch_split(const wd_gauge* gg, const DslashArgs& d, const LaunchCfg& c, hipStream_t s);
 
 template <class S, int BASIS>
 static void launch_cfg(const wd_gauge* gg, const DslashArgs& d, const LaunchCfg& c, hipStream_t s) {
   if (c.split) {
-    launch_split<S, BASIS>(gg, d, s);
+    launch_split<S, BASIS>(gg, d, c, s);
     return;
   }
   if constexpr (S::prec == WD_HALF_F16) {

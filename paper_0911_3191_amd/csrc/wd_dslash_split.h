@@ -372,8 +372,10 @@ __global__ void __launch_bounds__(512 / HPW, (split_waves<S, HPW, DOT>())) dslas
 
 // Geometry of a split launch: workgroups of 64 sites, four to each 256-site
 // record of the one-thread kernels (missing ones at the end write zeros).
-static DslashGeom make_split_geom(const Geom& geo, int nrhs) {
-  DslashGeom g = make_dgeom(geo, nrhs, LaunchCfg{1, 256});
+static DslashGeom make_split_geom(const Geom& geo, int nrhs, const LaunchCfg& c) {
+  LaunchCfg one{1, 256};
+  one.out_nt = c.out_nt;
+  DslashGeom g = make_dgeom(geo, nrhs, one);
   g.site_blocks *= 256 / kSplitSites;
   return g;
 }
@@ -407,8 +409,8 @@ static void launch_split_dot(int dot, unsigned grid, hipStream_t s, const Dslash
 }
 
 template <class S, int RECON, int BASIS, int HPW>
-static void launch_split_recon(const wd_gauge* gg, const DslashArgs& d, hipStream_t s) {
-  DslashGeom g = make_split_geom(gg->geom, d.rhs_map ? d.n_map : d.out.nrhs);
+static void launch_split_recon(const wd_gauge* gg, const DslashArgs& d, const LaunchCfg& c, hipStream_t s) {
+  DslashGeom g = make_split_geom(gg->geom, d.rhs_map ? d.n_map : d.out.nrhs, c);
   g.mapped = d.rhs_map ? 1 : 0;
   g.tgauge = gg->tgauge;
   const char* links = static_cast<const char*>(gg->link[S::prec]);
@@ -432,16 +434,16 @@ static void launch_split_recon(const wd_gauge* gg, const DslashArgs& d, hipStrea
 }
 
 template <class S, int BASIS>
-static void launch_split(const wd_gauge* gg, const DslashArgs& d, hipStream_t s) {
+static void launch_split(const wd_gauge* gg, const DslashArgs& d, const LaunchCfg& c, hipStream_t s) {
   if constexpr (S::prec == WD_FP64) {
     if ((int64_t)gg->geom.Vh * (d.rhs_map ? d.n_map : d.out.nrhs) > 65536) {
-      if (gg->recon == 8) launch_split_recon<S, 8, BASIS, 2>(gg, d, s);
-      else launch_split_recon<S, 12, BASIS, 2>(gg, d, s);
+      if (gg->recon == 8) launch_split_recon<S, 8, BASIS, 2>(gg, d, c, s);
+      else launch_split_recon<S, 12, BASIS, 2>(gg, d, c, s);
       return;
     }
   }
-  if (gg->recon == 8) launch_split_recon<S, 8, BASIS, 1>(gg, d, s);
-  else launch_split_recon<S, 12, BASIS, 1>(gg, d, s);
+  if (gg->recon == 8) launch_split_recon<S, 8, BASIS, 1>(gg, d, c, s);
+  else launch_split_recon<S, 12, BASIS, 1>(gg, d, c, s);
 }
 
 }  // namespace wd

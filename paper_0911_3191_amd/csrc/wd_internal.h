@@ -180,7 +180,7 @@ struct LaunchCfg {
   int wgs = 0;      // cap on workgroups per CU (0: registers decide)
   int lds = 0;      // 16-bit formats: stage x/y neighbours in LDS
   int rloop = 0;    // binary16, 12-real links: one thread per site loops over every RHS
-  int split = 0;    // one wavefront per hop (small launches); the fields above do not apply
+  int split = 0;    // one wavefront per hop (small launches); of the fields above only out_nt applies
 };
 void launch_dslash_cfg(const wd_gauge* g, wd_prec prec, const DslashArgs& d, const LaunchCfg& c,
                        hipStream_t s);
