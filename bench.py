@@ -128,10 +128,13 @@ def prepare_bytes(nrhs: int) -> int:
 
 
 def kernel_source_hash() -> str:
+    """Of the sources that the dslash launches are built from (every header) and
+    chosen by."""
     import hashlib
+    csrc = os.path.join(ROOT, "paper_0911_3191_amd", "csrc")
     h = hashlib.sha256()
-    for name in ("wd_dslash_impl.h", "wd_dslash.hip", "wd_device.h", "wd_reduce.h"):
-        with open(os.path.join(ROOT, "paper_0911_3191_amd", "csrc", name), "rb") as f:
+    for name in sorted(n for n in os.listdir(csrc) if n.endswith(".h")) + ["wd_dslash.hip", "wd_tune.cpp"]:
+        with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
 
