@@ -101,8 +101,8 @@ def bicgstab_iter_bytes(prec: str, nrhs: int) -> int:
     """One BiCGstab iteration for nrhs RHS, per site: 2 M_hat (4 dslash, the
     second of each with the xpay read and, for v, the <r~,v> read of r~) and
     the BLAS-1 passes (p: 3R+1W, s: 2R+1W, x/r: 5R+2W).  The method's passes,
-    kept as the measure of a step whatever the library fuses: its own
-    iteration reads r~ for both dots and updates x, r and p in one pass
+    kept as the measure of a step whatever the library fuses: below FP64 its
+    own iteration reads r~ for both dots and updates x, r and p in one pass
     (5R+3W), 2 spinors of 25 less."""
     s = SPINOR_B[prec]
     return (dslash_bytes(prec, nrhs) * 2 + dslash_bytes(prec, nrhs, 1) * 2 + nrhs * s  # <r~,v>
@@ -340,7 +340,7 @@ def oracle_checks(oracle, dims, U, x_host, x64_host, xtg_host, serve_kept, serve
 
 
 # ---- counter and trace summaries (no GPU: reads rocprofv3's CSV output) -------------
-DOT_NAMES = {0: "", 1: " <y,out>", 2: " <out,x>,|out|^2", 3: " |out|^2", 4: " res |r|^2", 5: " res->enc"}
+DOT_NAMES = {0: "", 1: " <y,out>", 2: " <out,x>,|out|^2,<y,out>,<y,x>,|x|^2", 3: " |out|^2", 4: " res |r|^2", 5: " res->enc"}
 PREC_OF = {"SF64": "fp64", "SF32": "fp32", "SI16": "i16", "SF16": "f16"}
 
 
@@ -384,7 +384,8 @@ def dslash_launch(name: str, grid: int, block: int, Vh: int, slab: bool) -> dict
     per_group = (8 * -(-(Vh // 8) // block) if slab else -(-Vh // block)) * block
     groups = grid // per_group if per_group else 0
     form = ("D^dag" if dag == "true" else "D") if xpay == "false" else \
-        ("x + a D^dag" if dag == "true" else "x + a D") + DOT_NAMES.get(dot, f" dot {dot}")
+        ("x + a D^dag" if dag == "true" else "x + a D") + \
+        (" <out,x>,|out|^2" if dot == 2 and prec == "fp64" else DOT_NAMES.get(dot, f" dot {dot}"))
     return {"prec": prec, "form": form, "basis": "UKQCD" if basis == 1 else "DR", "kind": kind,
             "lds": lds == "true", "block": block, "groups": groups,
             "nrhs": (nr * groups) if nr else None, "xpay": xpay == "true", "dot": dot}
@@ -437,7 +438,7 @@ def profile_summary(args) -> None:
     # xpay source and y where the form reads them
     def alg_reads(d):
         n = d["nrhs"] or NRHS
-        per = SPINOR_B[d["prec"]] * (1 + d["xpay"] + (d["dot"] in (1, 2, 4, 5)))
+        per = SPINOR_B[d["prec"]] * (1 + d["xpay"] + (d["dot"] in (1, 4, 5) or (d["dot"] == 2 and d["prec"] != "fp64")))
         return Vh * (8 * LINK_B[d["prec"]] + n * per)
 
     def label(d):
@@ -447,7 +448,7 @@ def profile_summary(args) -> None:
 
     h = kernel_source_hash()
     if args.profile_part == "trace":
-        print(f"Kernel source hash (wd_dslash_impl.h + wd_dslash.hip + wd_device.h + wd_reduce.h): `{h}`\n")
+        print(f"Kernel source hash (every header, wd_dslash.hip, wd_tune.cpp): `{h}`\n")
         print(f"## Timed dslash launches (the last {args.dslash_reps} of each group: the back-to-back launches "
               "bench.py times with HIP events)\n")
         print("| label | kernel | form | grid | launches | mean us | median us | min us | max us | algorithmic GB/s |")
@@ -474,7 +475,7 @@ def profile_summary(args) -> None:
         return
     if args.profile_part == "counters":
         # every counter of the run, median per labelled dslash group, with derived rates
-        print(f"Kernel source hash (wd_dslash_impl.h + wd_dslash.hip + wd_device.h + wd_reduce.h): `{h}`\n")
+        print(f"Kernel source hash (every header, wd_dslash.hip, wd_tune.cpp): `{h}`\n")
         names = sorted(cnt)
         groups = []
         for k in {k for rows in cnt.values() for k in rows}:

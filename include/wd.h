@@ -265,8 +265,9 @@ wd_status wd_mdagm_field(const wd_gauge *g, double kappa, void *out, const void 
  * process ends; (lattice, prec, nrhs) needing more than that
  * (wd_operator_workspace_bytes > 64 MiB: for one RHS FP64 above Vh = 87,360,
  * FP32 above Vh = 174,720, 16-bit above Vh = 322,624) are refused with
- * WD_EINVAL.  The launch shape is the tuned one if already known, else the
- * default (no tuning runs).  Allocates nothing.  All calls on one GPU share the array:
+ * WD_EINVAL.  The launch shape is, past the sizes that run one
+ * wavefront per hop, the tuned one if already known, else the default (no
+ * tuning runs).  Allocates nothing.  All calls on one GPU share the array:
  * calls that overlap in time on one GPU race, so the caller serialises them.
  * Asynchronous on stream. */
 wd_status mdagm_noalloc(const wd_gauge *g, double kappa, double *out, const double *in, wd_prec prec,

@@ -171,8 +171,9 @@ __global__ void __launch_bounds__(kBlock) k_bicg_xr(int Vh, FieldView x, FieldVi
 // p <- r + beta (p - omega v), unless the right-hand side pauses for a
 // reliable update, which re-seeds r first.  Eight fields moved; as an x/r update
 // with <r~, r> and |r|^2 and a p update it was eleven (and two launches more),
-// see FIN_BICG_STEP.  32^3x64, binary16, 12 RHS: 931 us (5.8 TB/s) instead of
-// 888 + 488; the launch that now also reads r~ takes 721 instead of 604.
+// see FIN_BICG_STEP.  32^3x64, binary16, 12 RHS: 956 us (5.6 TB/s) instead of
+// 888 + 488; the launch that now also reads r~ and sums in FP64 takes 806
+// instead of 604.  FP64 fields keep the two updates (k_bicg_xr, k_bicg_p).
 template <class S, bool SPLIT>
 __global__ void __launch_bounds__(kBlock) k_bicg_xrp(int Vh, FieldView x, FieldView r, FieldView p, FieldView t,
                                                      FieldView v, const double* __restrict__ sc,

@@ -197,14 +197,18 @@ __device__ __forceinline__ void decode_site(FieldView f, int r, int cb, double* 
 // and needs no other one; a record takes 13 slots of 16 bytes in the tile,
 // which spreads the lanes' own reads and writes over all banks.  Per pass
 // over a binary16 field at 48^3x96, 12 right-hand sides: encode 3.08 -> 2.89 ms,
-// decode 3.71 -> 2.79 ms; at 24^3x32, one: 10.6 -> 10.4 and 18.9 -> 11.2 us.
+// decode 3.71 -> 2.79 ms; at 24^3x32, one: 10.6 -> 10.3 and 18.9 -> 11.2 us.
 constexpr int kTileSites = 64;  // sites per workgroup, one wavefront
 constexpr int kTileRow = 13;    // 16-byte slots per record: 12 and one of padding
 
 // Moves the records of n consecutive lanes' sites between the canonical array
 // and the tile; rec: this lane's record number (CONTIG: those of the lanes
-// follow one another).  The library never reads back what it writes here, so
-// the stores are marked streaming (24^3x32 binary16 decode 11.2 -> 9.5 us).
+// follow one another).  The stores are marked streaming, so that the fields keep
+// the caches (24^3x32 binary16 decode 11.2 -> 10 us).  It holds for a caller who
+// feeds the output to the next call too: wilson_mat_pc applied again and again,
+// plain / streaming in microseconds, 8^4 FP64 14.5 / 14.4, 20x14x10x18 int16 with
+// 5 right-hand sides 36.5 / 36.5, binary16 24^3x32 54.2 / 54.4, 32^4 112.3 / 110.5,
+// 24^3x32 with 4 (170 MB of records) 161 / 154, 48^3x96 (1.02 GB) 1183 / 1149.
 template <bool CONTIG, bool STORE>
 __device__ __forceinline__ void move_records(double2* __restrict__ canon, double2* __restrict__ tile, int rec, int n) {
   const int lane = threadIdx.x;

@@ -125,7 +125,8 @@ enum DotMode { DOT_NONE = 0, DOT_YO = 1, DOT_OX = 2, DOT_OO = 3, DOT_RES = 4, DO
 
 // Full argument set of one dslash launch.  out = D in, or, with xpay set,
 // out = *xpay + a * D in; with xpay and dot set, per-block FP64 partials of
-// the dot products named by DotMode go to partials[rhs][block][4].  RHS whose
+// the dot products named by DotMode go to partials[rhs][block][4] (DOT_OX
+// below FP64: [8]).  RHS whose
 // active flag is 0 are skipped.
 // Spin bases of spinor fields (Appendix B): the caller's fields are in the
 // DeGrand-Rossi basis, the solvers rotate theirs into the UKQCD basis.
@@ -167,9 +168,10 @@ struct DslashArgs {
 };
 hipError_t launch_dslash_ex(const wd_gauge* g, wd_prec prec, const DslashArgs& d, hipStream_t s);
 
-// Launch shape of the dslash: right-hand sides per thread and threads per
-// workgroup.  The workgroup size is fixed at 256 so that fused dot products
-// reduce in the same order whatever the batch; only nr is tuned.
+// Launch shape of the dslash: right-hand sides per thread, threads per
+// workgroup and the rest that wd_tune.cpp searches.  Fused dot products keep
+// 256 threads and one sub-slab, so that they reduce in the same order whatever
+// the batch and the shape.
 struct LaunchCfg {
   int nr;
   int block;

@@ -678,10 +678,11 @@ hipError_t solver_issue(wd_solver* h) {
 }
 
 // Wait for the issued iterations, account for them, and launch the reliable
-// update of the RHS that triggered one, then their search-direction update.  Iterations are counted on the device (FL_ITERS); a reliable
-// update counts as one more (k + l).  The host waits for an update only where
-// it may end the solve of a right-hand side; the flags of the others come back
-// with the next iterations (one that converged all the same sits those out).
+// update of the RHS that triggered one, then their search-direction update.
+// Iterations are counted on the device (FL_ITERS); a reliable update counts as
+// one more (k + l).  The host waits for an update only where it may end the
+// solve of a right-hand side; the flags of the others come back with the next
+// iterations (one that converged all the same sits those out).
 wd_status solver_complete(wd_solver* h) {
   hipError_t e = hipStreamSynchronize(h->s);
   if (e != hipSuccess) return hip_fail(e, "solver iteration");
