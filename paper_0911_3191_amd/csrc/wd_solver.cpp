@@ -87,6 +87,7 @@ struct wd_solver {
   int per_check;     // inner iterations launched between two reads of the flags
   int loops;
   int batches;       // batches of per_check iterations launched
+  bool unread;       // a reliable update is under way whose flags the host has not read
   bool finished;
   hipGraph_t graph;
   hipGraphExec_t gexec;
@@ -564,6 +565,7 @@ wd_status wd_solver_begin(int32_t solver, const wd_gauge* g, double kappa, doubl
   h->finished = false;
   h->per_check = prm->check_every > 1 ? prm->check_every : 1;
   h->loops = 0;
+  h->unread = false;
   h->t0 = std::chrono::steady_clock::now();
   hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&h->h_sc),
                                (sizeof(double) * SC_COUNT + sizeof(int) * (FL_COUNT + 1)) * h->nrhs);
@@ -623,6 +625,14 @@ static hipError_t account(wd_solver* h) {
       h->status[k] = WD_OK;
     }
   }
+  return hipSuccess;
+}
+
+// The flags of a reliable update under way.
+static hipError_t read_update(wd_solver* h) {
+  WD_TRY(read_flags(h, false));
+  WD_TRY(account(h));
+  h->unread = false;
   return hipSuccess;
 }
 
@@ -688,6 +698,7 @@ wd_status solver_complete(wd_solver* h) {
   if (e != hipSuccess) return hip_fail(e, "solver iteration");
   e = account(h);
   if (e != hipSuccess) return hip_fail(e, "solver iteration");
+  h->unread = false;
   h->loops += h->per_check;
   bool any_ru = false, may_end = false;
   for (int k = 0; k < h->nrhs; ++k) {
@@ -709,9 +720,9 @@ wd_status solver_complete(wd_solver* h) {
       ++h->rus[k];
       h->iters[k] = h->h_fl[k * FL_COUNT + FL_ITERS] + h->rus[k];
     }
+    h->unread = true;
     if (may_end) {
-      e = read_flags(h, false);
-      if (e == hipSuccess) e = account(h);
+      e = read_update(h);
       if (e != hipSuccess) return hip_fail(e, "reliable update");
     }
   }
@@ -732,6 +743,11 @@ wd_status wd_solver_step(wd_solver* h, int32_t n_iters, int32_t* done) {
     if (e != hipSuccess) return hip_fail(e, "solver iteration");
     wd_status st = solver_complete(h);
     if (st) return st;
+  }
+  // the answer counts an update that converged before the host expected it to
+  if (h->unread && !solver_finished(h)) {
+    const hipError_t e = read_update(h);
+    if (e != hipSuccess) return hip_fail(e, "reliable update");
   }
   if (done) *done = solver_finished(h) ? 1 : 0;
   return WD_OK;

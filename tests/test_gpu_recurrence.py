@@ -73,3 +73,38 @@ def test_a_steep_step_brings_no_update_of_its_own(inner, restart, delta):
     st, infos = h.end()
     assert st == wd.WD_NOT_CONVERGED
     assert [(i["iters"], i["reliable_updates"]) for i in infos] == [(1, 0)] * NRHS
+
+
+@pytest.mark.parametrize("solver", ["bicgstab", "cg"])
+@pytest.mark.parametrize("inner", ["fp32", "f16"])
+def test_step_reports_an_update_that_converges(solver, inner):
+    """tol just above the true residual of a reliable update: the step that ran it
+    is the one that reports done, also where the iterated residual was still
+    above tol."""
+    dims, kappa = (6, 4, 6, 10), 0.124
+    s = Setup(dims, wdinputs.gauge_random(dims, 0.3, 7), precs=("fp64", inner))
+    bt = torch.from_numpy(np.ascontiguousarray(wdinputs.spinor_gaussian(dims, 8, nrhs=1))).to(DEV)
+
+    def steps(tol, most):
+        """(done, relative true residual at the last update) after each step."""
+        params = wd.solve_params(tol=tol, maxiter=2000, inner=inner, delta=0.1)
+        h = wd.Solver(solver, s.gauge, kappa, torch.zeros_like(bt), bt, params, wd.new_workspace(s.lat, params, solver))
+        out = []
+        while len(out) < most and not (out and out[-1][0]):
+            done = h.step(1)
+            q = h.residuals()[0]
+            out.append((done, float(np.sqrt(q[1] / q[2]))))
+        h.end()
+        return out
+
+    ref = steps(1e-13, 2000)
+    assert ref[-1][0]
+    best, tried = ref[0][1], 0
+    for k in range(1, len(ref)):
+        if ref[k][1] >= best:
+            continue
+        best = ref[k][1]
+        got = steps(best * (1 + 1e-12), k + 4)
+        assert [d for d, _ in got] == [False] * k + [True], k
+        tried += 1
+    assert tried >= 5
